@@ -46,12 +46,12 @@ int ok() {
 }  // namespace
 
 // Proposals per step of the QAP sweep: 0 = chosen per sweep by the kernel;
-// NMC_QAP_ROWS=1, 4 or 8 pins it, 2 pins the table mode, 3 the four
-// replicas per wave (for measurements; results do not change).
+// NMC_QAP_ROWS=1, 4 or 8 pins it, 16 pins whole rows, 2 the table mode, 3 the
+// four replicas per wave (for measurements; results do not change).
 static int32_t qap_rows_setting() {
     const char *e = std::getenv("NMC_QAP_ROWS");
     const int v = e ? std::atoi(e) : 0;
-    return (int32_t)(((v >= 1 && v <= 4) || v == 8) ? v : 0);
+    return (int32_t)(((v >= 1 && v <= 4) || v == 8 || v == kRowMode) ? v : 0);
 }
 
 // Whether the per-sweep choice of single-set QAP sweeps may take the table
@@ -2358,7 +2358,7 @@ int nmc_kernel_time(nmc_replicas *P, double *ms, int64_t *launches, double *atte
 struct BatchLaunch {
     int32_t what = 0;  // 0 k-SAT sweep, 1 QAP sweep, 2 k-SAT backbone, 3 QAP backbone
     size_t off_jobs = 0, off_items = 0;
-    int32_t n_items = 0, grid = 0, block = 0;
+    int32_t n_items = 0, grid = 0, block = 0;  // (QAP sweeps: block = 1 for row sweeps)
     size_t lds = 0;
     int32_t thr_num = 0, thr_den = 0, expand = 0;
     double attempts = 0;
@@ -2425,6 +2425,7 @@ struct BuiltPhase {
     size_t off_kjobs = 0, off_kitems = 0, off_qjobs = 0, off_qitems = 0;
     int nk_items = 0, nq_items = 0;
     size_t lds_k = 0, lds_q = 0;
+    QapBatchPlan plan_q;
     int grid_k = 0, grid_q = 0, block_k = 0;
     double attempts = 0;
 };
@@ -2561,6 +2562,7 @@ int build_batch(nmc_batch *B, const std::vector<PhaseSpec> &phases, bool with_ba
                 J.C.dstar = qmono && qap_dstar_setting();
                 J.C.key0 = (uint32_t)P->seed;
                 J.C.key1 = (uint32_t)(P->seed >> 32);
+                bp.plan_q.add(P->inst->n, J.C);
                 std::memcpy(blob.host.data() + bp.off_qjobs + j * sizeof(QapJob), &J, sizeof J);
                 const double n = P->inst->n;
                 const int blocks = (P->R + kQapRepPerBlock - 1) / kQapRepPerBlock;
@@ -2577,7 +2579,7 @@ int build_batch(nmc_batch *B, const std::vector<PhaseSpec> &phases, bool with_ba
                 std::memcpy(blob.host.data() + bp.off_qitems + t * sizeof(int2), &items[t].second, sizeof(int2));
             if (bp.lds_q > kLdsBytes)
                 return fail(NMC_ERR_CAPACITY, "batched QAP sweep needs %zu bytes of LDS", bp.lds_q);
-            bp.grid_q = std::min(bp.nq_items, qap_batch_occupancy(bp.lds_q) * cus);
+            bp.grid_q = std::min(bp.nq_items, qap_batch_occupancy(bp.plan_q) * cus);
         }
         built.push_back(bp);
         offset_sweeps += (uint32_t)ph.n_sweeps;
@@ -2643,7 +2645,7 @@ int enqueue_phase(nmc_batch *B, const BuiltPhase &bp, hipStream_t s) {
     if (bp.nq_items)
         HIP_OR_FAIL(qap_launch_sweep_batch(reinterpret_cast<const QapJob *>(B->dev + bp.off_qjobs),
                                            reinterpret_cast<const int2 *>(B->dev + bp.off_qitems), bp.nq_items,
-                                           bp.lds_q, bp.grid_q, s));
+                                           bp.plan_q.lds(), bp.plan_q.rows, bp.grid_q, s));
     return NMC_OK;
 }
 
@@ -2928,6 +2930,7 @@ int build_plans(nmc_batch *B, const std::vector<std::vector<SetPhase>> &ph, cons
         std::vector<QapJob> qj;
         std::vector<std::pair<double, int2>> kit, qit;
         size_t lds_k = 0, lds_q = 0;
+    QapBatchPlan plan_q;
         double att_k = 0, att_q = 0;
         for (size_t i = 0; i < ns; ++i) {
             const SetPhase *cur = nullptr;
@@ -2988,6 +2991,7 @@ int build_plans(nmc_batch *B, const std::vector<std::vector<SetPhase>> &ph, cons
                 for (int b = 0; b < blocks; ++b)
                     qit.push_back({nd * nd * nd, make_int2((int)qj.size(), b)});
                 lds_q = std::max(lds_q, qap_sweep_lds_bytes(P->inst->n, cur->nc, stride_q));
+                plan_q.add(P->inst->n, J.C);
                 att_q += (double)P->R * nd * (nd - 1) / 2.0 * len;
                 qj.push_back(J);
             }
@@ -3022,8 +3026,9 @@ int build_plans(nmc_batch *B, const std::vector<std::vector<SetPhase>> &ph, cons
             for (size_t t = 0; t < qit.size(); ++t)
                 std::memcpy(blob.host.data() + L.off_items + t * sizeof(int2), &qit[t].second, sizeof(int2));
             L.n_items = (int32_t)qit.size();
-            L.lds = lds_q;
-            L.grid = std::min(L.n_items, qap_batch_occupancy(lds_q) * cus);
+            L.lds = plan_q.lds();
+            L.block = plan_q.rows;
+            L.grid = std::min(L.n_items, qap_batch_occupancy(plan_q) * cus);
             L.attempts = att_q;
             launches.push_back(L);
         }
@@ -3041,8 +3046,8 @@ int enqueue_plan_launch(nmc_batch *B, const BatchLaunch &L, hipStream_t s) {
         break;
     case 1:
         HIP_OR_FAIL(qap_launch_sweep_batch(reinterpret_cast<const QapJob *>(d + L.off_jobs),
-                                           reinterpret_cast<const int2 *>(d + L.off_items), L.n_items, L.lds, L.grid,
-                                           s));
+                                           reinterpret_cast<const int2 *>(d + L.off_items), L.n_items, L.lds,
+                                           L.block != 0, L.grid, s));
         break;
     case 2:
         HIP_OR_FAIL(ksat_launch_backbone_batch(reinterpret_cast<const KsatJob *>(d + L.off_jobs),
@@ -3728,6 +3733,7 @@ extern "C" int nmc_batch_step(nmc_batch *B, const nmc_segment *segs, int32_t n_s
                off_bbqi = 0, off_src = 0, off_out = 0;
         int nk = 0, nq = 0, nbk = 0, nbq = 0;
         size_t lds_k = 0, lds_q = 0;
+    QapBatchPlan plan_q;
         for (int pass = 0; pass < 2; ++pass) {
             uint8_t *base = pass ? B->dev : nullptr;
             blob.host.clear();
@@ -3806,6 +3812,7 @@ extern "C" int nmc_batch_step(nmc_batch *B, const nmc_segment *segs, int32_t n_s
                     for (int b = 0; b < blocks; ++b)
                         qit.push_back({nd * nd * nd, make_int2((int)qj.size(), b)});
                     lds_q = std::max(lds_q, qap_sweep_lds_bytes(P->inst->n, nc, stride_q));
+                    plan_q.add(P->inst->n, J.C);
                     qj.push_back(J);
                     if (g.backbone_before) {
                         for (int f = 0; f < P->inst->n; ++f)
@@ -3876,10 +3883,10 @@ extern "C" int nmc_batch_step(nmc_batch *B, const nmc_segment *segs, int32_t n_s
                                                 block_k, grid, s));
         }
         if (nq) {
-            const int grid = std::min(nq, qap_batch_occupancy(lds_q) * cus);
+            const int grid = std::min(nq, qap_batch_occupancy(plan_q) * cus);
             HIP_OR_FAIL(qap_launch_sweep_batch(reinterpret_cast<const QapJob *>(B->dev + off_qjobs),
-                                               reinterpret_cast<const int2 *>(B->dev + off_qitems), nq, lds_q, grid,
-                                               s));
+                                               reinterpret_cast<const int2 *>(B->dev + off_qitems), nq,
+                                               plan_q.lds(), plan_q.rows, grid, s));
         }
         HIP_OR_FAIL(launch_set_status(reinterpret_cast<const SetStatusSrc *>(B->dev + off_src),
                                       reinterpret_cast<SetStatus *>(B->dev + off_out), (int)ns, s));

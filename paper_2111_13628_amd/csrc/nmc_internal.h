@@ -142,6 +142,21 @@ __host__ __device__ inline bool qap_tab_fits(int n, int rows, int stride) {
     return qap_base_lds(n, rows, stride) + qap_tab_lds(n) <= kLdsBytes;
 }
 
+// LDS of the row sweeps (nmc_qap.hip): both matrices as rows of
+// qap_row_stride bytes (two columns more than n; an odd multiple of 16, so that
+// the 16-byte operand reads of consecutive rows fall on different banks), with room for the
+// operand reads of the last, partly filled 64 rows; per wave a vector of a
+// byte per facility, one of words and the ring of acceptance bounds.
+__host__ __device__ inline int qap_row_stride(int n) { return 16 * (((n + 17) / 16) | 1); }
+__host__ __device__ inline int qap_ring_words(int n) { return n <= 64 ? 128 : n <= 192 ? 256 : 512; }
+__host__ __device__ inline size_t qap_row_mats(int n) {
+    return (align_up(n, 16) + align_up(n, 64)) * (size_t)qap_row_stride(n) + align_up(n, 64);
+}
+__host__ __device__ inline size_t qap_row_scratch(int n) {
+    return align_up(n, 64) * 5 + (size_t)qap_ring_words(n) * 4;
+}
+constexpr int kRowMode = 16;  // QapCall::rows: row sweeps pinned
+
 struct QapDev {
     const uint8_t *F;  // [n][n]
     const uint8_t *D;  // [n][n]
@@ -173,7 +188,7 @@ struct QapCall {
     int64_t target;
     int32_t check_start;
     uint32_t key0, key1;
-    int32_t rows;          // proposals per step: 0 = chosen per sweep, else 1, 4 or 8; 2 = table mode
+    int32_t rows;          // proposals per step: 0 = chosen per sweep, else 1, 4 or 8; 2 = table mode; 16 = whole rows
     int32_t tab_allow;     // the per-sweep choice may use the table mode (when its LDS fits)
     int32_t quad_allow;    // the per-sweep choice may run several replicas per wave: 0 no, 2 or 4 per wave
     int32_t reps_per_row;  // > 0: replica r reads table row r / reps_per_row (one [n_classes][stride] block per row)
@@ -235,15 +250,24 @@ hipError_t ksat_launch_pack(const uint8_t *x_rows, int n, int n_groups, int n_re
 
 // ---- launchers (nmc_qap.hip) ----
 size_t qap_sweep_lds_bytes(int n, int n_classes, int stride);
+size_t qap_rows_lds_bytes(int n, int table_rows, int stride, int waves);
+// LDS and kind of a batched sweep launch: row sweeps when every job's block
+// runs them and fits
+struct QapBatchPlan {
+    size_t rows_lds = 0, steps_lds = 0;
+    bool rows = true;
+    void add(int n, const QapCall &C);
+    size_t lds() const { return rows ? rows_lds : steps_lds; }
+};
 hipError_t qap_launch_init(const QapDev &I, const QapRepDev &R, uint32_t key0, uint32_t key1, hipStream_t s);
 hipError_t qap_launch_cost(const QapDev &I, const uint8_t *perm, int n_rep, int64_t *cost_out, hipStream_t s);
 hipError_t qap_launch_reset_tallies(const QapRepDev &R, int n, hipStream_t s);
 hipError_t qap_launch_sweep(const QapDev &I, const QapRepDev &R, const QapCall &C, int block_threads, hipStream_t s);
 hipError_t qap_launch_backbone(const QapDev &I, const QapRepDev &R, int thr_num, int thr_den, hipStream_t s);
 hipError_t qap_launch_tally(const QapRepDev &R, hipStream_t s);
-hipError_t qap_launch_sweep_batch(const QapJob *jobs, const int2 *items, int n_items, size_t lds, int grid,
+hipError_t qap_launch_sweep_batch(const QapJob *jobs, const int2 *items, int n_items, size_t lds, bool rows, int grid,
                                   hipStream_t s);
-int qap_batch_occupancy(size_t lds);
+int qap_batch_occupancy(const QapBatchPlan &plan);
 hipError_t qap_launch_backbone_batch(const QapJob *jobs, const int2 *items, int n_items, int thr_num, int thr_den,
                                      hipStream_t s);
 

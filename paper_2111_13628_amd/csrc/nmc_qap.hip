@@ -1,6 +1,13 @@
 // QAP kernels for gfx950.
 //
-// A workgroup of 16 waves owns 16 replicas, one per wave.  A wave evaluates
+// One wave runs one replica; F, D (bytes) and the sweep's threshold tables are
+// shared by a workgroup in LDS.  Two families of sweep kernels: the row sweeps
+// (qap_row_block, below; the default), and the stepped sweeps (qap_sweep_block),
+// kept for instances whose row sweeps do not fit in LDS, for tables that need
+// direct threshold reads and for the pinned widths, the table mode and
+// several replicas per wave.
+//
+// Stepped sweeps.  A workgroup of 16 waves owns 16 replicas.  A wave evaluates
 // four consecutive proposals of the lexicographic pair sequence at once, one
 // per 16-lane row, each row splitting the sum over facilities k among its
 // lanes; the decisions are then taken in sequence order: the first accepted
@@ -18,6 +25,7 @@
 // Assignment Problems"; cost sum_ij F_ij D_{p_i p_j}) exchanging the locations
 // of facilities a and b changes the cost by
 //   dC = 2 * sum_{k != a,b} (F_ak - F_bk) * (D_{p_b p_k} - D_{p_a p_k}).
+#include <algorithm>
 #include <climits>
 #include <type_traits>
 
@@ -28,6 +36,9 @@
 // `lane` of old; src and lane wave-uniform), which this toolchain's HIP
 // headers do not name.
 __device__ int nmc_amdgcn_writelane(int src, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
+// Its 24-bit signed product (v_mul_i32_i24, v_mad_i32_i24 with an add): plain
+// products of byte differences become quarter-rate 32- or 64-bit ones.
+__device__ int nmc_amdgcn_mul_i24(int a, int b) __asm("llvm.amdgcn.mul.i24.i32");
 
 namespace nmc {
 
@@ -35,6 +46,14 @@ namespace {
 
 constexpr int kRepPerBlock = kQapRepPerBlock;  // one replica per wave
 constexpr int kBlockThreads = 64 * kRepPerBlock;
+// A wave takes one proposal per step after a sweep that accepted more than
+// this many sixteenths of its proposals, else whole rows: the two break even
+// near 0.4 accepted with 4 waves per SIMD (n = 100, 4096 replicas: 16.1 and
+// 17.2 G proposals/s at 0.42, 15.6 and 11.4 at 0.69; in a batched launch 15.5
+// and 14.4 at 0.42) and near 0.65 with one (n = 150, 256 replicas: 1.20 and
+// 1.16 at 0.68, 1.21 and 1.76 at 0.40).
+constexpr int kRowAccMany = 6, kRowAccFew = 10;
+constexpr int kQapCus = 256;
 
 // Sum over the 16 lanes of each DPP row, returned to every lane of the row:
 // rotations by 8, 4, 2, 1 within the row.
@@ -558,6 +577,508 @@ __device__ __forceinline__ int qap_wave_sweep1(const QapDev &I, const QapCall &C
             pr[k] = (uint8_t)pk[i];
     }
     return n_acc;
+}
+
+// ---- row sweeps -----------------------------------------------------------
+//
+// The default sweep.  A wave runs one replica; a row of the pair order (a,
+// every b > a) is judged at once, lane k + 64 i holding facility k.  With
+//   h_k = sum_j F_aj D[p_k][p_j],  w_k = sum_j F_kj D[p_a][p_j],
+//   e_k = sum_j F_kj D[p_k][p_j]
+// the sum over every facility of (F_aj - F_kj)(D[p_k][p_j] - D[p_a][p_j]) is
+// h_k + w_k - e_k - e_a, so the cost change of the swap (a, k) is
+//   2 (h_k + w_k - e_k - e_a + 2 F_ak D[p_a][p_k])
+// (the j = a, k terms are -F_ak D[p_a][p_k] each).  Only differences of F and
+// of D enter, so both are kept shifted by -128 to signed bytes and h and w
+// are products of a fixed matrix with one vector on the matrix unit: w = F
+// times the row D[p_a][p_j], and h, in location order, D times F_a scattered
+// to the locations (16x16x64 signed-byte products, the vector in all 16 rows
+// of the first operand, so every result row is the product and a lane takes
+// its facility's column without moving data between lanes).  The first
+// accepted b of the row is the lowest bit of a ballot.  Accepting (a, b) moves
+// facility a to the old p_b, so with t_k = D[p_b][p_k] - D[p_a][p_k]
+//   e_k += (F_ak - F_bk) t_k,  h_k -= F_ab t_k   (k other than a, b),
+//   e_a = h_b + F_ab D_ab,  e_b = w_b + F_ab D_ab,
+// and w is one new product, of the 32-facility halves that still hold a later
+// b; the rest of the row is then judged again.  Decisions, words and
+// counters are those of the other paths.
+//
+// Measured (G proposals/s, kernel time, against the paths it replaced; n =
+// 100, 4096 replicas): 17.2 against 16.4 at 0.42 accepted, 39 against 15.4 at
+// 0.11, 86 against 31.6 at 0.003, 92 against 32.5 below 0.0002; 256 replicas
+// of n = 150: 1.76 / 4.3 / 10.3 against 0.88 / 0.87 / 1.37 at 0.40 / 0.10 /
+// 0.0015 (there mostly from spreading them over the CUs: qap_row_waves).
+// Bound at 4 waves per SIMD: the vector unit issues 64 % of the time (of the
+// ~200 vector instructions of a row of 50 proposals more than half draw the
+// words and their bounds), the matrix unit is busy 34 %, the LDS 56 %; with one
+// wave per SIMD it is the row's chain (gather, product, LDS exchange, product,
+// ballot).  Without the bounds' drawing the n = 100 case ran 1.25x, without
+// drawing and h 1.8x, without both products 2.1x as fast.
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+// Operands of the 32 rows from r0 of a shifted matrix of row stride S (two
+// tiles of 16 rows), tile = M + (lane % 16) S + 16 (lane / 16).  Rows past the
+// matrix read what follows it in LDS; their results are not used.
+template <int KPL>
+__device__ __forceinline__ void row_operands(const int8_t *tile, int S, int r0, v4i (&b)[2][KPL]) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int k = 0; k < KPL; ++k)
+            b[q][k] = *reinterpret_cast<const v4i *>(tile + (r0 + 16 * q) * S + 64 * k);
+}
+
+// The products of 32 rows of a matrix with the vector v: lane 16 g + c takes
+// column c of the tile g % 2 (every row of the result is the same).
+template <int KPL>
+__device__ __forceinline__ int row_half(const v4i (&b)[2][KPL], const v4i (&v)[KPL]) {
+    v4i c0 = {0, 0, 0, 0}, c1 = {0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < KPL; ++k) {
+        c0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(v[k], b[0][k], c0, 0, 0, 0);
+        c1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(v[k], b[1][k], c1, 0, 0, 0);
+    }
+    return threadIdx.x & 16 ? c1[0] : c0[0];
+}
+
+// A vector of a byte per lane as the matrix unit's first operand: the 16
+// bytes of the lane's 16-lane row, in every lane (bytes placed by lane, joined
+// within quads, the quads' words broadcast along the row: no trip through
+// LDS).
+__device__ __forceinline__ v4i row_vector(int x) {
+    const uint32_t sel = 0x0C0C0C0Cu & ~(0xFFu << (8 * (threadIdx.x & 3)));
+    int w = (int)__builtin_amdgcn_perm(0u, (uint32_t)x, sel);
+    w |= __builtin_amdgcn_update_dpp(0, w, 0xB1, 0xF, 0xF, true);  // quad_perm [1,0,3,2]
+    w |= __builtin_amdgcn_update_dpp(0, w, 0x4E, 0xF, 0xF, true);  // quad_perm [2,3,0,1]
+    v4i v;
+    v[0] = __builtin_amdgcn_update_dpp(0, w, 0x150, 0xF, 0xF, true);  // row_newbcast of lanes 0, 4, 8, 12
+    v[1] = __builtin_amdgcn_update_dpp(0, w, 0x154, 0xF, 0xF, true);
+    v[2] = __builtin_amdgcn_update_dpp(0, w, 0x158, 0xF, 0xF, true);
+    v[3] = __builtin_amdgcn_update_dpp(0, w, 0x15C, 0xF, 0xF, true);
+    return v;
+}
+
+// Order LDS accesses of one wave that cross lanes (the hardware keeps a
+// wave's LDS accesses in order; this keeps the compiler from moving them).
+__device__ __forceinline__ void lds_order() { __asm__ volatile("" ::: "memory"); }
+
+// Value of x at facility 64 s + l, and x with v written there (s and l
+// wave-uniform).
+template <int KPL>
+__device__ __forceinline__ int fac_read(const int (&x)[KPL], int s, int l) {
+    int r = __builtin_amdgcn_readlane(x[0], l);
+#pragma unroll
+    for (int i = 1; i < KPL; ++i)
+        if (s == i)
+            r = __builtin_amdgcn_readlane(x[i], l);
+    return r;
+}
+template <int KPL>
+__device__ __forceinline__ void fac_write(int (&x)[KPL], int s, int l, int v) {
+#pragma unroll
+    for (int i = 0; i < KPL; ++i)
+        if (KPL == 1 || s == i)
+            x[i] = lane_write(x[i], l, v);
+}
+
+// e_k of every facility from the permutation.
+template <int KPL>
+__device__ __forceinline__ void row_diagonal(const int8_t *F, const int8_t *D, int S, int n, const int (&pk)[KPL],
+                                             int (&e)[KPL]) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < KPL; ++i)
+        e[i] = 0;
+#pragma unroll
+    for (int s = 0; s < KPL; ++s) {
+        const int l_end = min(64, n - 64 * s);
+#pragma unroll 4
+        for (int l = 0; l < l_end; ++l) {
+            const int pj = __builtin_amdgcn_readlane(pk[s], l);
+#pragma unroll
+            for (int i = 0; i < KPL; ++i)
+                e[i] += nmc_amdgcn_mul_i24((int)F[(64 * s + l) * S + lane + 64 * i], (int)D[pj * S + pk[i]]);
+        }
+    }
+}
+
+// One sweep of one replica, row by row; pk and e (in and out) the
+// permutation and the diagonal sums.  A row is judged 32 facilities (two
+// tiles of w) at a time: after an accepted swap only the 32 that hold the
+// next b are multiplied again, the later ones once they are reached.
+// Per-wave LDS: F_a in location order (64 KPL bytes), h in location order
+// (64 KPL words) and a ring of acceptance bounds that holds one row and the
+// 64 of a generator call.  Distance rows end in a column of -128 (a distance
+// of 0: the lane of facility a reads it while row a runs, so that its entry
+// of D[p_a][.] stays right whatever p_a is) and one of 0 (lanes past n: they
+// add nothing).  Returns the number of accepted swaps.
+template <int NH, bool HF, bool HD>
+__device__ __forceinline__ int qap_wave_sweep_rows(const QapDev &I, const QapCall &C, const int8_t *F,
+                                                   const int8_t *D, const int S, const uint8_t *cls,
+                                                   const uint32_t *tw, uint8_t *scr, int (&pk)[(NH + 1) / 2],
+                                                   int (&e)[(NH + 1) / 2], uint32_t t, uint32_t group, int word,
+                                                   long long &cost) {
+    constexpr int KPL = (NH + 1) / 2;
+    const int n = I.n;
+    const int lane = threadIdx.x & 63;
+    const bool one_class = C.n_classes == 1;
+    int8_t *fq = reinterpret_cast<int8_t *>(scr);
+    int *hst = reinterpret_cast<int *>(fq + 64 * KPL), *ring = hst + 64 * KPL;
+    const int rmask = qap_ring_words(n) - 1;
+    const int toff = (lane & 15) * S + 16 * (lane >> 4);
+    const int8_t *ft = F + toff, *dt = D + toff;
+    const v4i *fop = reinterpret_cast<const v4i *>(fq + 16 * (lane >> 4));
+    const bool tail = lane + 64 * (KPL - 1) < n;   // the lane's last slot holds a facility
+    v4i fh[NH][2][KPL], dh[NH][2][KPL];            // HF, HD: the operands of F, of D
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+        if constexpr (HF)
+            row_operands<KPL>(ft, S, 32 * h, fh[h]);
+        if constexpr (HD)
+            row_operands<KPL>(dt, S, 32 * h, dh[h]);
+    }
+    fq[lane + 64 * (KPL - 1)] = 0;  // locations past n stay zero
+    int n_acc = 0;
+    int gen = 0;     // bounds drawn so far
+    int rowend = 0;  // pair index past row a
+    for (int a = 0; a < n - 1; ++a) {
+        const int sa = a >> 6, la = a & 63;
+        const int idx0 = rowend - a - 1;  // pair (a, k) is idx0 + k
+        rowend += n - 1 - a;
+        while (gen < rowend) {
+            ring[(gen + lane) & rmask] =
+                (int)((qap_lane_word(I, C, tw, cls, one_class, (uint32_t)(gen + lane), t, group, word) + 1) >> 1);
+            gen += 64;
+        }
+        int pa = fac_read<KPL>(pk, sa, la);
+        int ea = fac_read<KPL>(e, sa, la);
+        int fa[KPL], f2[KPL], va[KPL], h[KPL], ys[KPL];
+#pragma unroll
+        for (int i = 0; i < KPL; ++i) {
+            fa[i] = F[a * S + lane + 64 * i];
+            va[i] = D[pa * S + pk[i]];
+        }
+        lds_order();
+#pragma unroll
+        for (int i = 0; i < KPL; ++i)
+            if (i < KPL - 1 || tail)
+                fq[pk[i]] = (int8_t)fa[i];
+        lds_order();
+        fac_write<KPL>(pk, sa, la, n);
+        v4i vv[KPL], fv[KPL];
+#pragma unroll
+        for (int k = 0; k < KPL; ++k) {
+            fv[k] = fop[4 * k];
+            vv[k] = row_vector(va[k]);
+        }
+#pragma unroll
+        for (int i = 0; i < KPL; ++i) {
+            int x[2] = {0, 0};
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (2 * i + q < NH) {
+                    if constexpr (HD) {
+                        x[q] = row_half<KPL>(dh[2 * i + q], fv);
+                    } else {
+                        v4i b[2][KPL];
+                        row_operands<KPL>(dt, S, 64 * i + 32 * q, b);
+                        x[q] = row_half<KPL>(b, fv);
+                    }
+                }
+            hst[lane + 64 * i] = lane & 32 ? x[1] : x[0];
+        }
+        lds_order();
+#pragma unroll
+        for (int i = 0; i < KPL; ++i) {
+            // 2 F_ak D[p_a][p_k] = f2 (va + 128), its constant part kept in h
+            f2[i] = 2 * (fa[i] + 128);
+            h[i] = hst[pk[i]] + 128 * f2[i];
+            ys[i] = ring[(idx0 + lane + 64 * i) & rmask];
+        }
+        lds_order();
+        // w of 32 facilities against the current row of D
+        auto product = [&](int s, int q) {
+            if constexpr (HF) {
+                return row_half<KPL>(fh[2 * s + q], vv);
+            } else {
+                v4i b[2][KPL];
+                row_operands<KPL>(ft, S, 64 * s + 32 * q, b);
+                return row_half<KPL>(b, vv);
+            }
+        };
+        // half the cost change of every pair of the row against its bound
+        int w0[KPL];
+        uint64_t m0[KPL], any = 0;
+#pragma unroll
+        for (int s = 0; s < KPL; ++s) {
+            int x[2] = {0, 0};
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (2 * s + q < NH && 64 * s + 32 * q + 32 > a + 1)
+                    x[q] = product(s, q);
+            w0[s] = lane & 32 ? x[1] : x[0];
+            const int y = h[s] - e[s] + w0[s] - ea + nmc_amdgcn_mul_i24(f2[s], va[s]);
+            const int k = lane + 64 * s;
+            m0[s] = __ballot(y < ys[s] && k > a && k < n);
+            any |= m0[s];
+        }
+        bool moved = false;  // a swap of this row was accepted: w0 and m0 are stale
+#pragma unroll
+        for (int s = 0; s < KPL; ++s)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int r0 = 64 * s + 32 * q;
+                if (2 * s + q >= NH || !any || r0 + 32 <= a + 1)
+                    continue;
+                // the half's undecided lanes (k > a and k < n)
+                uint64_t open = 0xFFFFFFFFull << (32 * q);
+                if (r0 <= a)
+                    open &= (~0ull << la) << 1;
+                if (64 * s + 32 * q + 32 > n)
+                    open &= ~(~0ull << (n - 64 * s));
+                while (open) {
+                    const int w = moved ? product(s, q) : w0[s];
+                    const int y = h[s] - e[s] + w - ea + nmc_amdgcn_mul_i24(f2[s], va[s]);
+                    const uint64_t m = __ballot(y < ys[s]) & open;
+                    if (!m)
+                        break;
+                    const int lb = __builtin_ctzll(m), b = 64 * s + lb;
+                    open &= (~0ull << lb) << 1;
+                    const int yb = __builtin_amdgcn_readlane(y, lb);
+                    const int pb = __builtin_amdgcn_readlane(pk[s], lb);
+                    pk[s] = lane_write(pk[s], lb, pa);
+                    int fb[KPL], vn[KPL];
+#pragma unroll
+                    for (int i = 0; i < KPL; ++i) {
+                        fb[i] = F[b * S + lane + 64 * i];
+                        vn[i] = D[pb * S + pk[i]];
+                    }
+                    const int fab = __builtin_amdgcn_readlane(fa[s], lb) + 128;
+                    const int fd = fab * (__builtin_amdgcn_readlane(va[s], lb) + 128);
+                    const int wb = __builtin_amdgcn_readlane(w, lb);
+                    ea = __builtin_amdgcn_readlane(h[s], lb) - 256 * fab + fd;
+                    cost += 2 * yb;
+                    ++n_acc;
+#pragma unroll
+                    for (int i = 0; i < KPL; ++i) {
+                        const int d = vn[i] - va[i];
+                        e[i] += nmc_amdgcn_mul_i24(fa[i] - fb[i], d);
+                        h[i] -= nmc_amdgcn_mul_i24(fab, d);
+                        va[i] = vn[i];
+                        vv[i] = row_vector(va[i]);
+                    }
+                    e[s] = lane_write(e[s], lb, wb + fd);
+                    pa = pb;
+                    moved = true;
+                }
+            }
+        fac_write<KPL>(pk, sa, la, pa);
+        fac_write<KPL>(e, sa, la, ea);
+    }
+    return n_acc;
+}
+
+// One sweep, one proposal at a time on all 64 lanes (the algorithm of
+// qap_wave_sweep1 on the shifted matrices, the permutation staying in the
+// lanes): for sweeps where most proposals are accepted.
+template <int KPL>
+__device__ __forceinline__ int qap_wave_sweep_pairs(const QapDev &I, const QapCall &C, const int8_t *F,
+                                                    const int8_t *D, const int S, const uint8_t *cls,
+                                                    const uint32_t *tw, int (&pk)[KPL], uint32_t t, uint32_t group,
+                                                    int word, long long &cost) {
+    const int n = I.n;
+    const int lane = threadIdx.x & 63;
+    const bool one_class = C.n_classes == 1;
+    int n_acc = 0, widx = 0;
+    uint32_t pbase = 0;
+    uint32_t dsv = qap_lane_word(I, C, tw, cls, one_class, (uint32_t)lane, t, group, word);
+    int csum = 0;  // at most 64 accepted changes of |dC| <= 2 (n - 2) 255^2
+#pragma unroll
+    for (int SA = 0; SA < KPL; ++SA) {
+        const int a_end = min(n - 1, 64 * SA + 64);
+        for (int a = 64 * SA; a < a_end; ++a) {
+            const int la = a - 64 * SA;
+            int pa = __builtin_amdgcn_readlane(pk[SA], la);
+            int fa[KPL], da[KPL];
+#pragma unroll
+            for (int i = 0; i < KPL; ++i) {
+                fa[i] = F[a * S + lane + 64 * i];
+                da[i] = D[pa * S + pk[i]];
+            }
+            // the cached row's distance at k = a: 0 when gathered, the
+            // accepted swap's D_{p_a p_b} after an accept
+            int g = 0;
+#pragma unroll
+            for (int SB = SA; SB < KPL; ++SB) {
+                const int b_end = min(n, 64 * SB + 64);
+                for (int b = max(a + 1, 64 * SB); b < b_end; ++b) {
+                    const int lb = b - 64 * SB;
+                    const int pb = __builtin_amdgcn_readlane(pk[SB], lb);
+                    int db[KPL];
+                    int part = 0;
+#pragma unroll
+                    for (int i = 0; i < KPL; ++i) {
+                        const int fb = F[b * S + lane + 64 * i];
+                        db[i] = D[pb * S + pk[i]];
+                        part += nmc_amdgcn_mul_i24(fa[i] - fb, db[i] - da[i]);
+                    }
+                    const int fab = __builtin_amdgcn_readlane(fa[SB], lb) + 128;
+                    const int dab = __builtin_amdgcn_readlane(da[SB], lb) + 128;
+                    const int dc = 2 * (wave_sum(part) + fab * (2 * dab - g));
+                    const int ds = __builtin_amdgcn_readlane((int)dsv, widx);
+                    if (dc < ds) {
+                        ++n_acc;
+                        csum += dc;
+                        pk[SA] = lane_write(pk[SA], la, pb);
+                        pk[SB] = lane_write(pk[SB], lb, pa);
+#pragma unroll
+                        for (int i = 0; i < KPL; ++i)
+                            da[i] = db[i];
+                        da[SB] = lane_write(da[SB], lb, dab - 128);
+                        g = dab;
+                        pa = pb;
+                    }
+                    if (++widx == 64) {
+                        widx = 0;
+                        pbase += 64;
+                        dsv = qap_lane_word(I, C, tw, cls, one_class, pbase + (uint32_t)lane, t, group, word);
+                        cost += csum;
+                        csum = 0;
+                    }
+                }
+            }
+        }
+    }
+    cost += csum;
+    return n_acc;
+}
+
+// n_sweeps sweeps of the replicas of block blk (one per wave), by the whole
+// workgroup of W = blockDim.x / 64 waves.  Each wave chooses per sweep, from
+// the acceptance of its last one, between row sweeps and one proposal per
+// step.  With `mix` (tempering, n_rep a multiple of W, W of 8 or 16) wave w
+// runs replica 4 (blk + (w / 4) B) + w % 4, B = 4-replica quads per slot, and
+// reads the table row of its quad.
+// NH = n / 32 rounded up (a block may take a larger one of the same KPL).
+template <int NH, bool FEW>
+__device__ __forceinline__ void qap_row_block(const QapDev &I, const QapRepDev &R, const QapCall &C, const int blk,
+                                              const bool mix, uint8_t *smem) {
+    constexpr int KPL = (NH + 1) / 2;
+    const int n = I.n, S = qap_row_stride(n);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int W = blockDim.x >> 6;
+    const int npairs = n * (n - 1) / 2;
+    const int tab_words = C.n_classes * C.stride;
+    const int nslots = mix ? W / 4 : 1;
+    int8_t *F = reinterpret_cast<int8_t *>(smem);
+    int8_t *D = F + align_up(n, 16) * S;
+    uint8_t *scr = smem + qap_row_mats(n) + (size_t)wave * qap_row_scratch(n);
+    uint8_t *cls = smem + qap_row_mats(n) + (size_t)W * qap_row_scratch(n);
+    uint32_t *tl = reinterpret_cast<uint32_t *>(cls + align_up(n, 16));
+    const int quads = R.n_rep / W;
+    auto rep_of = [&](int w) { return mix ? 4 * (blk + (w >> 2) * quads) + (w & 3) : blk * W + w; };
+    auto row_of = [&](int slot) {
+        return C.tab + (C.reps_per_row > 0 ? (size_t)(rep_of(4 * slot) / C.reps_per_row) * tab_words : 0);
+    };
+    // both matrices shifted to signed bytes; two columns end the rows of D
+    // (see qap_wave_sweep_rows)
+    for (int r = wave; r < n; r += W)
+        for (int k = lane; k < n + 2; k += 64) {
+            if (k < n)
+                F[r * S + k] = (int8_t)(I.F[r * n + k] ^ 0x80u);
+            D[r * S + k] = k < n ? (int8_t)(I.D[r * n + k] ^ 0x80u) : k == n ? (int8_t)-128 : (int8_t)0;
+        }
+    for (int i = tid; i < n; i += blockDim.x)
+        cls[i] = C.fac_cls ? C.fac_cls[i] : 0;
+
+    const int rep = rep_of(wave);
+    const bool active = rep < R.n_rep;  // wave-uniform
+    const uint32_t *tw = tl + (mix ? (wave >> 2) * tab_words : 0);
+    const uint32_t group = (uint32_t)rep >> 2;
+    const int word = rep & 3;
+    int pk[KPL], e[KPL];
+    long long cost = 0, best = 0;
+    unsigned long long acc_total = 0;
+    int fh = -1, rows = kRowMode;
+    bool diag = false;  // e holds this permutation's sums
+#pragma unroll
+    for (int i = 0; i < KPL; ++i) {
+        const int k = lane + 64 * i;
+        pk[i] = k < n ? (active ? R.perm[(size_t)rep * n + k] : 0) : n + 1;
+        e[i] = 0;
+    }
+    if (active) {
+        rows = C.rows ? C.rows : R.rows_hint[rep] == 1 ? 1 : kRowMode;
+        cost = R.cost[rep];
+        best = R.best[rep];
+        fh = R.first_hit[rep];
+        if (C.check_start && fh < 0 && cost <= C.target)
+            fh = (int)C.t0;
+    }
+    for (int s = 0; s < C.n_sweeps; ++s) {
+        const uint32_t t = C.t0 + (uint32_t)s;
+        __syncthreads();
+        for (int q = 0; q < nslots; ++q) {
+            const uint32_t *tg = row_of(q) + (size_t)s * C.sweep_words;
+            for (int i = tid; i < tab_words; i += blockDim.x)
+                tl[q * tab_words + i] = tg[i];
+        }
+        __syncthreads();
+        if (!active)
+            continue;
+        int n_acc;
+        if (__builtin_amdgcn_readfirstlane(rows) == 1) {
+            diag = false;
+            n_acc = qap_wave_sweep_pairs<KPL>(I, C, F, D, S, cls, tw, pk, t, group, word, cost);
+        } else {
+            if (!diag)
+                row_diagonal<KPL>(F, D, S, n, pk, e);
+            diag = true;
+            n_acc = qap_wave_sweep_rows<NH, FEW || KPL <= 2, FEW && KPL <= 3>(I, C, F, D, S, cls, tw, scr, pk, e, t, group, word, cost);
+        }
+        acc_total += (unsigned long long)n_acc;
+        if (C.rows == 0)
+            rows = 16 * n_acc > (FEW ? kRowAccFew : kRowAccMany) * npairs ? 1 : kRowMode;
+        // sweep end
+        if (cost < best) {
+            best = cost;
+#pragma unroll
+            for (int i = 0; i < KPL; ++i)
+                if (lane + 64 * i < n)
+                    R.best_perm[(size_t)rep * n + lane + 64 * i] = (uint8_t)pk[i];
+        }
+        if (fh < 0 && cost <= C.target)
+            fh = (int)(t + 1);
+    }
+    if (active) {
+#pragma unroll
+        for (int i = 0; i < KPL; ++i)
+            if (lane + 64 * i < n)
+                R.perm[(size_t)rep * n + lane + 64 * i] = (uint8_t)pk[i];
+        if (lane == 0) {
+            R.cost[rep] = cost;
+            R.best[rep] = best;
+            R.first_hit[rep] = fh;
+            if (C.rows == 0)
+                R.rows_hint[rep] = (uint8_t)(rows == 1 ? 1 : 8);
+            if (acc_total)
+                atomicAdd(R.accepted, acc_total);
+        }
+    }
+}
+
+template <typename Fn>
+__device__ __forceinline__ void qap_dispatch_rows(int n, Fn &&fn) {
+    using std::integral_constant;
+    if (n <= 64)
+        fn(integral_constant<int, 2>{});
+    else if (n <= 128)
+        fn(integral_constant<int, 4>{});
+    else if (n <= 192)
+        fn(integral_constant<int, 6>{});
+    else
+        fn(integral_constant<int, 8>{});
 }
 
 // ---- table mode -----------------------------------------------------------
@@ -1190,16 +1711,33 @@ __global__ void __launch_bounds__(1024) qap_sweep_kernel(QapDev I, QapRepDev R, 
     });
 }
 
-// Batched launch over (job, block of 16 replicas) items in decreasing cost.
+// The default sweep launch: W = blockDim.x / 64 replicas per workgroup.
+// FEW: four waves to a workgroup, at most two on a SIMD, so registers hold the
+// matrices' operands.
+template <int NH, bool FEW>
+__global__ void __launch_bounds__(FEW ? 256 : NH <= 6 ? 1024 : 512)
+    qap_rows_kernel(QapDev I, QapRepDev R, QapCall C, bool mix) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    qap_row_block<NH, FEW>(I, R, C, blockIdx.x, mix, smem);
+}
+
+// Batched launch over (job, block of 16 replicas) items in decreasing cost:
+// row sweeps, or the stepped kernel when a job cannot run them.
+template <bool ROWS>
 __global__ void __launch_bounds__(1024) qap_sweep_batch_kernel(const QapJob *jobs, const int2 *items, int n_items) {
     extern __shared__ __align__(16) uint8_t smem[];
     for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
         const int2 w = items[it];
         const QapJob &J = jobs[w.x];
-        qap_dispatch_kpl(J.I.n, [&](auto k4, auto k1, auto k8) {
-            qap_sweep_block<decltype(k4)::value, decltype(k1)::value, decltype(k8)::value, 0>(J.I, J.R, J.C, w.y,
-                                                                                             false, smem);
-        });
+        if constexpr (ROWS)
+            qap_dispatch_rows(J.I.n, [&](auto nh) {
+                qap_row_block<decltype(nh)::value, false>(J.I, J.R, J.C, w.y, false, smem);
+            });
+        else
+            qap_dispatch_kpl(J.I.n, [&](auto k4, auto k1, auto k8) {
+                qap_sweep_block<decltype(k4)::value, decltype(k1)::value, decltype(k8)::value, 0>(J.I, J.R, J.C, w.y,
+                                                                                                 false, smem);
+            });
         __syncthreads();
     }
 }
@@ -1292,8 +1830,82 @@ hipError_t qap_launch_reset_tallies(const QapRepDev &R, int n, hipStream_t s) {
     return hipMemcpyAsync(R.best_perm, R.perm, (size_t)R.n_rep * n, hipMemcpyDeviceToDevice, s);
 }
 
+size_t qap_rows_lds_bytes(int n, int table_rows, int stride, int waves) {
+    return qap_row_mats(n) + (size_t)waves * qap_row_scratch(n) + align_up(n, 16) +
+           align_up((size_t)table_rows * stride * sizeof(uint32_t), 16);
+}
+
+// Waves per workgroup of a row-sweep launch (0: the block does not fit in
+// LDS) and its LDS.  The fewest waves that still put min(16, replicas / CU)
+// waves on every CU: small sets spread over all CUs (256 replicas of n = 150
+// as 16 workgroups of 16 waves left 240 CUs idle), large ones share F, D
+// and the thresholds among 8 or 16 replicas.
+static int qap_row_waves(int n, const QapCall &C, int n_rep, size_t *lds_out, bool *mix_out) {
+    const int need = std::min(16, (n_rep + kQapCus - 1) / kQapCus);
+    int pick = 0, pick_res = 0;
+    for (int W = 4; W <= (n <= 192 ? 16 : 8); W *= 2) {
+        const bool can_mix = W > 4 && C.reps_per_row > 0 && C.reps_per_row % 4 == 0 && n_rep % W == 0;
+        for (int mix = can_mix ? 1 : 0; mix >= 0; --mix) {
+            const size_t lds = qap_rows_lds_bytes(n, C.n_classes * (mix ? W / 4 : 1), C.stride, W);
+            if (lds > kLdsBytes)
+                continue;
+            // (four waves to a workgroup: the registers leave room for 8 or 4)
+            const int res = W * std::min<int>((int)(kLdsBytes / lds), W == 4 ? (n <= 128 ? 2 : 1) : 16 / W);
+            if (res > pick_res && pick_res < need) {
+                pick = W;
+                pick_res = res;
+                *lds_out = lds;
+                *mix_out = mix != 0;
+            }
+            break;
+        }
+    }
+    return pick;
+}
+
+// whether a call's settings leave the sweep kind to the row sweeps
+static bool qap_rows_asked(const QapCall &C) {
+    return C.dstar && (C.rows == 0 || C.rows == 1 || C.rows == kRowMode) && !C.tab_allow && !C.quad_allow;
+}
+
+void QapBatchPlan::add(int n, const QapCall &C) {
+    const size_t lds = qap_rows_lds_bytes(n, C.n_classes, C.stride, kRepPerBlock);
+    rows_lds = std::max(rows_lds, lds);
+    steps_lds = std::max(steps_lds, qap_base_lds(n, C.n_classes, C.stride));
+    rows = rows && qap_rows_asked(C) && lds <= kLdsBytes;
+}
+
 hipError_t qap_launch_sweep(const QapDev &I, const QapRepDev &R, const QapCall &C, int block_threads, hipStream_t s) {
     (void)block_threads;
+    if (qap_rows_asked(C)) {
+        size_t lds = 0;
+        bool mix = false;
+        const int W = qap_row_waves(I.n, C, R.n_rep, &lds, &mix);
+        if (W) {
+            using Kernel = void (*)(QapDev, QapRepDev, QapCall, bool);
+            static const Kernel kernels[2][8] = {
+                {qap_rows_kernel<1, false>, qap_rows_kernel<2, false>, qap_rows_kernel<3, false>,
+                 qap_rows_kernel<4, false>, qap_rows_kernel<5, false>, qap_rows_kernel<6, false>,
+                 qap_rows_kernel<7, false>, qap_rows_kernel<8, false>},
+                {qap_rows_kernel<1, true>, qap_rows_kernel<2, true>, qap_rows_kernel<3, true>,
+                 qap_rows_kernel<4, true>, qap_rows_kernel<5, true>, qap_rows_kernel<6, true>,
+                 qap_rows_kernel<7, true>, qap_rows_kernel<8, true>}};
+            static const hipError_t attr = [] {
+                hipError_t e = hipSuccess;
+                for (const auto &few : kernels)
+                    for (const Kernel f : few)
+                        if (e == hipSuccess)
+                            e = hipFuncSetAttribute((const void *)f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                    (int)kLdsBytes);
+                return e;
+            }();
+            if (attr != hipSuccess)
+                return attr;
+            hipLaunchKernelGGL(kernels[W == 4][(I.n - 1) / 32], dim3((R.n_rep + W - 1) / W), dim3(64 * W), lds, s, I,
+                               R, C, mix);
+            return hipGetLastError();
+        }
+    }
     // quads of four temperatures per workgroup when their four table rows fit
     const size_t lds_mix = qap_sweep_lds_bytes(I.n, 4 * C.n_classes, C.stride);
     const bool mix = C.reps_per_row > 0 && C.reps_per_row % 4 == 0 && R.n_rep % kRepPerBlock == 0 &&
@@ -1323,21 +1935,31 @@ hipError_t qap_launch_sweep(const QapDev &I, const QapRepDev &R, const QapCall &
     return hipGetLastError();
 }
 
-hipError_t qap_launch_sweep_batch(const QapJob *jobs, const int2 *items, int n_items, size_t lds, int grid,
+hipError_t qap_launch_sweep_batch(const QapJob *jobs, const int2 *items, int n_items, size_t lds, bool rows, int grid,
                                   hipStream_t s) {
     // once per process (thread-safe initialization)
-    static const hipError_t attr = hipFuncSetAttribute((const void *)qap_sweep_batch_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                       (int)kLdsBytes);
+    static const hipError_t attr = [] {
+        hipError_t e = hipSuccess;
+        for (const void *f : {(const void *)qap_sweep_batch_kernel<false>, (const void *)qap_sweep_batch_kernel<true>})
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
+        return e;
+    }();
     if (attr != hipSuccess)
         return attr;
-    hipLaunchKernelGGL(qap_sweep_batch_kernel, dim3(grid), dim3(kBlockThreads), lds, s, jobs, items, n_items);
+    if (rows)
+        hipLaunchKernelGGL(qap_sweep_batch_kernel<true>, dim3(grid), dim3(kBlockThreads), lds, s, jobs, items, n_items);
+    else
+        hipLaunchKernelGGL(qap_sweep_batch_kernel<false>, dim3(grid), dim3(kBlockThreads), lds, s, jobs, items,
+                           n_items);
     return hipGetLastError();
 }
 
-int qap_batch_occupancy(size_t lds) {
+int qap_batch_occupancy(const QapBatchPlan &plan) {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void *)qap_sweep_batch_kernel, kBlockThreads, lds) !=
-        hipSuccess)
+    const void *f =
+        plan.rows ? (const void *)qap_sweep_batch_kernel<true> : (const void *)qap_sweep_batch_kernel<false>;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f, kBlockThreads, plan.lds()) != hipSuccess)
         return 1;
     return nb < 1 ? 1 : nb;
 }

@@ -230,3 +230,26 @@ def test_qap_direct_threshold_reads_match_oracle(monkeypatch):
         cls = p.backbone(2, 3)
         p.anneal(reanneal_profile(4, sc), profile="backbone", class_of=cls)
         p.compare()
+
+
+@pytest.mark.parametrize("n,R,hi", [(2, 3, 99), (16, 4, 255), (31, 9, 99), (33, 2100, 99), (48, 7, 255), (64, 20, 99),
+                                    (65, 6, 255), (96, 5, 99), (112, 12, 99), (129, 4, 99), (150, 1040, 60),
+                                    (193, 5, 99)])
+def test_qap_row_sweeps(n, R, hi, monkeypatch):
+    """Whole-row sweeps pinned (and then chosen per sweep), from mostly accepted
+    to mostly rejected, on both sides of every operand size (32 and 64
+    facilities), with entries on both sides of the signed byte, and at replica
+    counts that take four and eight waves per workgroup; integer results, so
+    exact."""
+    F, D = instances.gen_qap(n, SEED + 5 * n, 0, hi)
+    sc = beta_scale(F, D, samples=300) if n > 3 else 1e-3
+    S = 6 if n < 100 else 3
+    for rows in ("16", "0"):
+        say(f"case: qap rows={rows} n={n} R={R}")
+        monkeypatch.setenv("NMC_QAP_ROWS", rows)
+        p = QapPair(F, D, R, SEED + n)
+        p.anneal(np.geomspace(0.05 * sc, 8.0 * sc, S)[None, :], target=0)
+        p.compare()
+        cls = p.backbone(2, 3)
+        p.anneal(reanneal_profile(2, sc), profile="backbone", class_of=cls)
+        p.compare()
