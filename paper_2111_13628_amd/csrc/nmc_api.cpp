@@ -187,6 +187,10 @@ struct nmc_instance {
     size_t off_lbp_caddr = 0, off_lbp_pos = 0;
     std::vector<int32_t> lbp_pos;
     uint32_t rec_bytes = 0;  // size of the record array
+    // split layout (see KsatDev)
+    size_t off_sp_rec = 0, off_sp_var = 0, off_sp_info = 0, off_sp_color = 0;
+    uint32_t sp_rec_bytes = 0;
+    int32_t sp_lg = 0, sp_chunks = 0, sp_waves = 0;
     // wide layout (spins in device memory; see nmc_ksat_wide.hip)
     bool wide = false;
     size_t off_wrec = 0, off_worder = 0, off_wclass = 0;
@@ -218,6 +222,14 @@ struct nmc_instance {
         d.var_cl = reinterpret_cast<const int32_t *>(dev + off_var_cl);
         d.lbp_caddr = reinterpret_cast<const uint32_t *>(dev + off_lbp_caddr);
         d.lbp_pos = reinterpret_cast<const int32_t *>(dev + off_lbp_pos);
+        d.sp_rec = reinterpret_cast<const uint64_t *>(dev + off_sp_rec);
+        d.sp_var = reinterpret_cast<const int2 *>(dev + off_sp_var);
+        d.sp_info = reinterpret_cast<const int2 *>(dev + off_sp_info);
+        d.sp_color = reinterpret_cast<const int32_t *>(dev + off_sp_color);
+        d.sp_rec_bytes = sp_rec_bytes;
+        d.sp_lg = sp_lg;
+        d.sp_chunks = sp_chunks;
+        d.sp_waves = sp_waves;
         d.wrec = reinterpret_cast<const uint4 *>(dev + off_wrec);
         d.worder = reinterpret_cast<const int32_t *>(dev + off_worder);
         d.wclass_ptr = reinterpret_cast<const int32_t *>(dev + off_wclass);
@@ -283,6 +295,12 @@ struct ChunkRec {
     uint32_t a[3];
     uint32_t neg;
 };
+
+// The 8-byte record of the sweeps: three addresses, then the sign.
+uint64_t pack_rec(const ChunkRec &r) {
+    return (uint64_t)r.a[0] | ((uint64_t)r.a[1] << kAddrBits) | ((uint64_t)r.a[2] << (2 * kAddrBits)) |
+           ((uint64_t)r.neg << (3 * kAddrBits));
+}
 
 // Bank model of one byte gather on gfx950 LDS: 32 banks of 4 bytes, a wave's
 // 64 addresses served in two half-waves of 32; lanes reading the same dword
@@ -584,7 +602,7 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
             };
             const size_t n_rec = vcl.size();
             const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
-            const unsigned nt = bank_schedule && n_rec >= 200000 ? std::min(8u, hw) : 1u;
+            const unsigned nt = bank_schedule && n_rec >= 20000 ? std::min(8u, hw) : 1u;
             std::vector<std::thread> pool;
             for (unsigned t = 1; t < nt; ++t)
                 pool.emplace_back(worker);
@@ -606,9 +624,7 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
             for (int32_t sl = 0; sl < nslot; ++sl)
                 for (int lane = 0; lane < kChunk; ++lane) {
                     const ChunkRec &r = placed[(size_t)sl * kChunk + lane];
-                    rec[base + (size_t)(sl / 2) * 2 * kChunk + (size_t)lane * 2 + (sl & 1)] =
-                        (uint64_t)r.a[0] | ((uint64_t)r.a[1] << kAddrBits) | ((uint64_t)r.a[2] << (2 * kAddrBits)) |
-                        ((uint64_t)r.neg << (3 * kAddrBits));
+                    rec[base + (size_t)(sl / 2) * 2 * kChunk + (size_t)lane * 2 + (sl & 1)] = pack_rec(r);
                 }
         }
         I->n_chunks = (int32_t)chunk_info.size();
@@ -616,6 +632,85 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
             std::fprintf(stderr, "nmc: %d chunks, %lld slot gathers, modeled %.3f LDS cycles per gather\n",
                          I->n_chunks, (long long)model_gathers, (double)model_cycles / (double)model_gathers);
         }  // !I->wide
+        // split layout: every class's variables on 2^lg lanes each (lg fixed per
+        // instance: a class then fills about four waves, one per SIMD), the
+        // clauses dealt round-robin over a variable's lanes
+        std::vector<uint64_t> sp_rec;
+        std::vector<int32_t> sp_color(ncol + 1, 0);
+        std::vector<int2> sp_info, sp_var;
+        if (!I->wide && split && n <= kSplitMaxVars && (int64_t)n <= (int64_t)kSplitMaxClass * ncol) {
+            int32_t lg = 2;
+            while (lg < kMaxSplitLog && ((int64_t)n << (lg + 1)) <= (int64_t)256 * ncol)
+                ++lg;
+            const int32_t L = 1 << lg, per = kChunk >> lg;
+            struct SplitChunk {
+                std::vector<std::vector<ChunkRec>> lanes;
+                std::vector<ChunkRec> placed;
+            };
+            std::vector<SplitChunk> work;
+            int32_t rows = 0;
+            for (int32_t c = 0; c < ncol; ++c) {
+                std::vector<int32_t> vs(I->order.begin() + I->color_ptr[c], I->order.begin() + I->color_ptr[c + 1]);
+                std::stable_sort(vs.begin(), vs.end(), [&](int32_t x, int32_t y) {
+                    return (vptr[x + 1] - vptr[x]) > (vptr[y + 1] - vptr[y]);
+                });
+                for (size_t b = 0; b < vs.size(); b += per) {
+                    const size_t e = std::min(vs.size(), b + per);
+                    // (descending degrees: the first variable has the most clauses)
+                    const int32_t slots = std::max(1, (vptr[vs[b] + 1] - vptr[vs[b]] + L - 1) / L);
+                    const int32_t pairs = (slots + 1) / 2;
+                    sp_info.push_back(make_int2(rows, pairs));
+                    rows += pairs;
+                    SplitChunk w;
+                    w.lanes.resize(kChunk);
+                    std::vector<int32_t> n1(kChunk, 0);
+                    for (size_t i = b; i < e; ++i) {
+                        const int32_t v = vs[i];
+                        for (int32_t q = vptr[v]; q < vptr[v + 1]; ++q) {
+                            const int32_t a = vcl[q], own = vpos[q], lane = (int32_t)(i - b) * L + (q - vptr[v]) % L;
+                            ChunkRec r{{ZERO, ZERO, ZERO}, lits[own] < 0 ? 1u : 0u};
+                            int k = 0;
+                            for (int32_t p = clause_ptr[a]; p < clause_ptr[a + 1]; ++p)
+                                if (p != own)
+                                    r.a[k++] = lit_addr(lits[p]);
+                            n1[lane] += (int32_t)r.neg;
+                            w.lanes[lane].push_back(r);
+                        }
+                    }
+                    work.push_back(std::move(w));
+                    for (int lane = 0; lane < kChunk; ++lane) {
+                        const size_t i = b + (size_t)(lane >> lg);
+                        const uint32_t kk = (uint32_t)(2 * pairs - 2 * n1[lane]) * 0x01010101u - (uint32_t)n1[lane] +
+                                            (lane % L ? 0u : 0x80808080u);
+                        sp_var.push_back(make_int2(i < e ? vs[i] : -1, (int32_t)kk));
+                    }
+                }
+                sp_color[c + 1] = (int32_t)sp_info.size();
+                I->sp_waves = std::max(I->sp_waves, std::min(16, sp_color[c + 1] - sp_color[c]));
+            }
+            const ChunkRec dummy{{ONES, ZERO, ZERO}, 0u};
+            std::atomic<size_t> next{0};
+            auto worker = [&] {
+                for (size_t i; (i = next.fetch_add(1)) < work.size();)
+                    schedule_chunk(work[i].lanes, 2 * sp_info[i].y, bank_schedule, work[i].placed, dummy);
+            };
+            const unsigned nt =
+                bank_schedule && vcl.size() >= 20000 ? std::min(8u, std::max(1u, std::thread::hardware_concurrency())) : 1u;
+            std::vector<std::thread> pool;
+            for (unsigned t = 1; t < nt; ++t)
+                pool.emplace_back(worker);
+            worker();
+            for (auto &t : pool)
+                t.join();
+            sp_rec.resize((size_t)rows * kChunk * 2);
+            for (size_t i = 0; i < work.size(); ++i)
+                for (int32_t sl = 0; sl < 2 * sp_info[i].y; ++sl)
+                    for (int lane = 0; lane < kChunk; ++lane)
+                        sp_rec[(size_t)(sp_info[i].x + sl / 2) * 2 * kChunk + (size_t)lane * 2 + (sl & 1)] =
+                            pack_rec(work[i].placed[(size_t)sl * kChunk + lane]);
+            I->sp_lg = lg;
+            I->sp_chunks = (int32_t)sp_info.size();
+        }
         // wide layout: per incidence (var_ptr order) the clause's other
         // literals as spin-table rows (v for x_v, n + 1 + v for NOT x_v, row
         // n: absent, never true), and whether the variable's own literal is
@@ -681,6 +776,13 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
             I->off_lbp_caddr = ar.take(std::max<size_t>(lbp_caddr.size() * 4, 16));
             I->off_lbp_pos = ar.take(std::max<size_t>(I->lbp_pos.size() * 4, 4));
         }
+        if (I->sp_lg) {
+            I->off_sp_rec = ar.take(sp_rec.size() * 8);
+            I->sp_rec_bytes = (uint32_t)(sp_rec.size() * 8);
+            I->off_sp_var = ar.take(sp_var.size() * 8);
+            I->off_sp_info = ar.take(sp_info.size() * 8);
+            I->off_sp_color = ar.take(sp_color.size() * 4);
+        }
         if (I->wide) {
             I->off_wrec = ar.take(std::max<size_t>(wrec.size() * sizeof(uint4), 16));
             I->off_worder = ar.take((size_t)n * 4);
@@ -702,6 +804,12 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
         if (!I->wide) {
             put(I->off_lbp_caddr, lbp_caddr.data(), lbp_caddr.size() * 4);
             put(I->off_lbp_pos, I->lbp_pos.data(), I->lbp_pos.size() * 4);
+        }
+        if (I->sp_lg) {
+            put(I->off_sp_rec, sp_rec.data(), sp_rec.size() * 8);
+            put(I->off_sp_var, sp_var.data(), sp_var.size() * 8);
+            put(I->off_sp_info, sp_info.data(), sp_info.size() * 8);
+            put(I->off_sp_color, sp_color.data(), sp_color.size() * 4);
         }
         if (I->wide) {
             put(I->off_wrec, wrec.data(), wrec.size() * sizeof(uint4));

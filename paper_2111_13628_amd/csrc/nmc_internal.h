@@ -47,6 +47,11 @@ constexpr int kSlotUnroll = 4;  // clause slots per chunk are padded to a multip
 constexpr int kSplitShift = 16;
 constexpr int kMaxSplitLog = 4;
 
+// The split layout: instances of at most kSplitMaxVars variables whose colour
+// classes hold kSplitMaxClass variables or fewer on average.
+constexpr int kSplitMaxVars = 12288;
+constexpr int kSplitMaxClass = 256;
+
 // LDS available to one workgroup on gfx950.
 constexpr size_t kLdsBytes = 160 * 1024;
 
@@ -65,6 +70,15 @@ struct KsatDev {
     const int32_t *lbp_pos;      // [M] position of each clause in the LBP clause order
     int32_t n, m, n_colors, n_chunks, dmax;
     uint32_t rec_bytes;          // size of rec in bytes (the bound of the sweep's buffer loads)
+    // split layout (small colour classes; sp_lg = 0: none): each variable on
+    // 2^sp_lg lanes in every chunk, records in 16-byte pairs of slots
+    const uint64_t *sp_rec;      // [pair-row][64 lanes][2]
+    const int2 *sp_var;          // [sp_chunks][64] variable (-1: empty lane) and the constant part of the
+                                 // lane's share of the closed form (the 128s on the first lane)
+    const int2 *sp_info;         // [sp_chunks] (first pair-row, pairs)
+    const int32_t *sp_color;     // [n_colors + 1] chunk range of each colour class
+    uint32_t sp_rec_bytes;
+    int32_t sp_lg, sp_chunks, sp_waves;  // sp_waves: most chunks of a class, at most 16
     // wide layout (wide != 0; rec and the chunk arrays are then empty)
     const uint4 *wrec;           // [sum deg] per incidence in var_ptr order: the clause's other three
                                  // literals as row | negated << 31 (row N: absent, never true), own sign

@@ -21,7 +21,7 @@
 // equals the sequential colour-major order.  The instance (per-variable
 // clause records) streams from L2/MALL, shared by every workgroup.
 #include <climits>
-#include <cstdlib>
+#include <type_traits>
 
 #include "nmc_internal.h"
 #include "nmc_philox.h"
@@ -73,6 +73,14 @@ typedef __attribute__((address_space(3))) uint8_t lds_u8;
 // dynamic LDS block starts at address 0 and spin-table offsets are addresses.
 __device__ __forceinline__ uint32_t lds_load_u8(uint32_t a) { return *(lds_cu8 *)(uintptr_t)a; }
 __device__ __forceinline__ void lds_store_u8(uint32_t a, uint32_t v) { *(lds_u8 *)(uintptr_t)a = (uint8_t)v; }
+
+// The three gathered bytes and the sign mask of one clause slot (below).
+__device__ __forceinline__ void slot_gather(uint2 r, uint32_t (&x)[3], uint32_t &sm) {
+    x[0] = lds_load_u8(r.x & kAddrMask);
+    x[1] = lds_load_u8(__builtin_amdgcn_alignbit(r.y, r.x, kAddrBits) & kAddrMask);
+    x[2] = lds_load_u8(__builtin_amdgcn_ubfe(r.y, 2 * kAddrBits - 32, kAddrBits));
+    sm = (uint32_t)__builtin_amdgcn_sbfe(r.y, 3 * kAddrBits - 32, 1);
+}
 
 // One clause slot: r.x bits 0..16 and r.y bits 0..1 / 2..18 hold the spin-table
 // addresses of the clause's three other literals, r.y bit 19 whether the
@@ -173,10 +181,7 @@ __device__ __forceinline__ void slot_step2(uint32_t &a0, uint32_t &a1, uint2 r) 
 // and 2g + 1, held in one spin byte per variable (first group in bits 0..3),
 // so every clause record, address decode and LDS gather serves 8 replicas;
 // the random words and every result are those of the groups run one by one.
-// STAGED: the instance's records and chunk tables are copied into LDS at the
-// start (instances small enough for them to fit beside the spin tables), so
-// a colour class's loads are LDS reads instead of L2 round trips.
-template <int GPW, bool STAGED = false>
+template <int GPW>
 __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &R, const SweepCall &C, const int g,
                                             uint8_t *smem) {
     constexpr int NR = kGroup * GPW;  // replicas of the item
@@ -237,27 +242,6 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
     }
     if (tid < 16)
         red[tid] = 0;
-    // staged instance: records, chunk descriptors, lane words, class ranges
-    uint4 *s_rec = nullptr, *s_u = nullptr;
-    int2 *s_info = nullptr;
-    int *s_var = nullptr, *s_cc = nullptr;
-    if constexpr (STAGED) {
-        uint8_t *st = (uint8_t *)(red + 16);
-        s_rec = (uint4 *)st;
-        s_info = (int2 *)(st + align_up(I.rec_bytes, 16));
-        s_var = (int *)((uint8_t *)s_info + align_up((size_t)I.n_chunks * 8, 16));
-        s_cc = s_var + (size_t)I.n_chunks * kChunk;
-        // each variable's random words of the current sweep
-        s_u = (uint4 *)((uint8_t *)s_cc + align_up(((size_t)I.n_colors + 1) * 4, 16));
-        for (int w = tid; w < (int)(I.rec_bytes / 16); w += nthr)
-            s_rec[w] = reinterpret_cast<const uint4 *>(I.rec)[w];
-        for (int w = tid; w < I.n_chunks; w += nthr)
-            s_info[w] = I.chunk_info[w];
-        for (int w = tid; w < I.n_chunks * kChunk / 4; w += nthr)
-            reinterpret_cast<int4 *>(s_var)[w] = reinterpret_cast<const int4 *>(I.chunk_var)[w];
-        for (int w = tid; w <= I.n_colors; w += nthr)
-            s_cc[w] = I.color_chunk[w];
-    }
     int E = 0, best = 0, fh = -1;
     if (tid < nact) {
         E = R.energy[r0 + tid];
@@ -277,15 +261,6 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
         const uint32_t *tg = tab + (size_t)s * C.sweep_words;
         for (int i = tid; i < tab_words; i += nthr)
             tl[i] = tg[i];
-        if constexpr (STAGED) {
-            // a staged (small, latency-bound) instance draws the sweep's
-            // random words of every variable at once, spread over the whole
-            // workgroup, instead of one dependent generator chain per colour
-            // class (the words depend only on the variable, the sweep and the
-            // group, so drawing them for every variable changes nothing)
-            for (int w = tid; w < n; w += nthr)
-                s_u[w] = philox4x32_10((uint32_t)w, t, (uint32_t)g0, kStreamKsatSweep, C.key0, C.key1);
-        }
         __syncthreads();
 
         int dsum[NR];
@@ -293,7 +268,7 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
         for (int j = 0; j < NR; ++j)
             dsum[j] = 0;
         for (int c = 0; c < I.n_colors; ++c) {
-            const int h0 = STAGED ? s_cc[c] : I.color_chunk[c], h1 = STAGED ? s_cc[c + 1] : I.color_chunk[c + 1];
+            const int h0 = I.color_chunk[c], h1 = I.color_chunk[c + 1];
             // chunks of a class are sorted by slot count (descending); rounds
             // alternate direction so heavy and light chunks pair up per wave
             const int nch = h1 - h0;
@@ -310,10 +285,10 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
                     __builtin_amdgcn_s_sleep(4);
                 if (wave_u & 1)
                     __builtin_amdgcn_s_sleep(2);
-                const int2 info = STAGED ? s_info[h] : I.chunk_info[h];
+                const int2 info = I.chunk_info[h];
                 const int nslot = __builtin_amdgcn_readfirstlane(info.y & ((1 << kSplitShift) - 1));
                 const int lg = __builtin_amdgcn_readfirstlane(info.y >> kSplitShift);
-                const int lw = STAGED ? s_var[h * kChunk + lane] : I.chunk_var[(size_t)h * kChunk + lane];
+                const int lw = I.chunk_var[(size_t)h * kChunk + lane];
                 // with lg > 0 a variable's clauses are spread over 2^lg lanes;
                 // the first of them takes the decision
                 const int v = (lw < 0 || (lane & ((1 << lg) - 1))) ? -1 : (lw & 0xFFFFF);
@@ -325,8 +300,6 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
                 // instruction computes a record address
                 const int row0 = __builtin_amdgcn_readfirstlane(info.x) / 2;
                 auto rp = [&](int row) -> uint4 {
-                    if constexpr (STAGED)
-                        return s_rec[(row0 + row) * kChunk + lane];
                     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
                                                          recs, lane * 16, (row0 + row) * (kChunk * 16), 0));
                 };
@@ -379,11 +352,8 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
 #pragma unroll
                 for (int k = 0; k < GPW; ++k) {
                     uint32_t part = ((uint32_t)nslot - 2u * nneg) * 0x01010101u - nneg - acc[k];
-                    if constexpr (STAGED)
-                        part = lane_group_sum(part, lg);
-                    else
-                        for (int off = 1; off < (1 << lg); off <<= 1)
-                            part += (uint32_t)__shfl_xor((int)part, off, 64);
+                    for (int off = 1; off < (1 << lg); off <<= 1)
+                        part += (uint32_t)__shfl_xor((int)part, off, 64);
                     acc[k] = 0x80808080u + part;
                 }
                 if (v >= 0) {
@@ -405,9 +375,8 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
                     for (int k = 0; k < GPW; ++k) {
                         // one generator call per group gives its 4 replicas' words
                         if ((need >> (4 * k)) & 0xFu) {
-                            const uint4 u = STAGED ? s_u[v]
-                                                   : philox4x32_10((uint32_t)v, t, (uint32_t)(g0 + k),
-                                                                   kStreamKsatSweep, C.key0, C.key1);
+                            const uint4 u = philox4x32_10((uint32_t)v, t, (uint32_t)(g0 + k), kStreamKsatSweep,
+                                                          C.key0, C.key1);
                             const int b = 4 * k;
                             flip |= (((need >> b) & 1u) && u.x < thr[b]) ? 1u << b : 0u;
                             flip |= (((need >> (b + 1)) & 1u) && u.y < thr[b + 1]) ? 2u << b : 0u;
@@ -517,18 +486,271 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
         atomicAdd(R.accepted, acc_w);
 }
 
+// ---- split sweeps -----------------------------------------------------------
+//
+// Instances of small colour classes.  A class of a few hundred variables is a
+// few chunks of 64, one lane each, so of the 16 waves of a workgroup most
+// waited at every class barrier while a few walked 40 records per lane, and
+// what bounds a sweep is the latency of one class step.  Here every variable
+// has 2^LG lanes (the split layout: each walks 1 / 2^LG of its records, all
+// gathers in flight at once), the four lanes of its first quad decide one
+// replica each, the records of a wave's next chunk are loaded while this
+// one is decided, the random words are drawn by whole waves (one generator
+// call per lane serves the wave's next 2^LG chunks), and thresholds, best
+// states and classes stay in LDS: a sweep ends with one barrier and no
+// access to device memory.
+//
+// Measured (us per sweep at 64 to 1024 replicas, default tuning, against one
+// lane per variable with the words drawn per class, records staged in LDS at n
+// = 200): 4-SAT n = 200 34.6 -> 16.3, 1000 77 -> 24, 2000 93 -> 37, 5000 104 ->
+// 47, 9000 105 -> 63; 3-SAT n = 1000 23 -> 10.3, 3500 25.2 -> 18.6.  A class
+// step of n = 200 takes 0.5 us: gathers, sum, threshold read, store and
+// barrier in sequence.  At n = 5000 the gathers' bank conflicts counted (56 us
+// before the records were placed by bank) and so did 32-bit multiplies and a
+// table read under a mask in the decision.
+//
+// LDS: x and not-x (2 n + 2 bytes), best states (n), classes (2 n), two sweeps'
+// threshold rows, the energy sums of two sweeps, and per wave its list of
+// chunks, their variables (4 bytes each) and 64 generator blocks.
+struct SplitLds {
+    size_t best, cls, tl, red, list, list_len, vars, words, total;
+};
+__host__ __device__ inline SplitLds split_lds(int n, int n_colors, int n_chunks, int lg, int tab_words, int waves) {
+    SplitLds L;
+    L.best = align_up(2 * (size_t)n + 2, 16);
+    L.cls = L.best + align_up(n, 16);
+    L.tl = L.cls + align_up(2 * (size_t)n, 16);
+    L.red = L.tl + align_up(2 * (size_t)tab_words * 4, 16);
+    L.list = L.red + 32;
+    // a wave has at most one more chunk per class than its even share
+    L.list_len = (size_t)n_colors + (size_t)(n_chunks + waves - 1) / waves;
+    L.vars = L.list + L.list_len * waves * 16;
+    L.words = L.vars + align_up(L.list_len * waves * (kChunk >> lg) * 4, 16);
+    L.total = L.words + (size_t)waves * kChunk * 16;
+    return L;
+}
+
+template <int LG>
+__global__ void __launch_bounds__(1024) ksat_split_kernel(KsatDev I, KsatRepDev R, SweepCall C) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    constexpr int PER = kChunk >> LG;  // variables of a chunk
+    // record pairs of the next chunk loaded ahead: 48 clauses per variable
+    constexpr int PRE = LG == 2 ? 6 : LG == 3 ? 4 : 3;
+    const int n = I.n, g = blockIdx.x;
+    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, nwaves = nthr >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tab_words = C.n_classes * C.stride;
+    const SplitLds L = split_lds(n, I.n_colors, I.sp_chunks, LG, tab_words, nwaves);
+    uint8_t *xt = smem, *bx = smem + L.best;
+    uint16_t *cls = (uint16_t *)(smem + L.cls);  // threshold row offset of each variable's class
+    uint32_t *tl = (uint32_t *)(smem + L.tl);
+    int *red = (int *)(smem + L.red);
+    int4 *list = (int4 *)(smem + L.list) + wave * L.list_len;
+    int *vars = (int *)(smem + L.vars) + wave * L.list_len * PER;
+    uint4 *words = (uint4 *)(smem + L.words) + wave * kChunk;
+
+    const int r0 = g * kGroup, nact = min(kGroup, R.n_rep - r0);
+    const uint32_t amask = (1u << nact) - 1u;
+    const int j = lane & 3;  // the replica this lane decides
+    uint8_t *xg = R.xs + (size_t)g * n, *bg = R.best_xs + (size_t)g * n;
+    for (int v = tid; v < n; v += nthr) {
+        const uint32_t b = xg[v] & amask;
+        xt[v] = (uint8_t)b;
+        xt[n + v] = (uint8_t)(~b & amask);
+        bx[v] = bg[v];
+        cls[v] = C.var_cls ? (uint16_t)(C.var_cls[v] * C.stride) : 0;
+    }
+    if (tid == 0) {
+        xt[2 * n] = 0;
+        xt[2 * n + 1] = (uint8_t)amask;
+    }
+    if (tid < 8)
+        red[tid] = 0;
+    const uint32_t *tab = C.tab + (C.reps_per_row > 0 ? (size_t)(r0 / C.reps_per_row) * tab_words : 0);
+    if (C.n_sweeps > 0)
+        for (int i = tid; i < tab_words; i += nthr)
+            tl[i] = tab[i];
+    // the wave's chunks in class order: (chunk, class, first pair-row, pairs)
+    int items = 0;
+    for (int c = 0; c < I.n_colors; ++c)
+        for (int h = I.sp_color[c] + wave; h < I.sp_color[c + 1]; h += nwaves) {
+            const int2 info = I.sp_info[h];
+            list[items] = make_int4(h, c, info.x, info.y);  // (every lane the same)
+            if (lane < PER)
+                vars[items * PER + lane] = max(I.sp_var[(size_t)h * kChunk + (lane << LG)].x, 0);
+            ++items;
+        }
+    int E = 0, best = 0, fh = -1;
+    if (j < nact) {
+        E = R.energy[r0 + j];
+        best = R.best[r0 + j];
+        fh = R.first_hit[r0 + j];
+        if (C.check_start && fh < 0 && E <= C.target)
+            fh = (int)C.t0;
+    }
+    const __amdgpu_buffer_rsrc_t recs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t *>(I.sp_rec), 0, (int)I.sp_rec_bytes, kBufferWord3);
+    uint4 q[PRE];
+    int lw = -1;
+    uint32_t kk = 0;
+    int4 e = make_int4(0, 0, 0, 0);  // the chunk's list entry
+    auto rp = [&](int row) -> uint4 {
+        return __builtin_bit_cast(
+            uint4, __builtin_amdgcn_raw_buffer_load_b128(recs, lane * 16, row * (kChunk * 16), 0));
+    };
+    // loads of the chunk of entry e: lane words and the first records (rows
+    // past the chunk are other chunks' or, past the end, zeros; they are not
+    // used)
+    auto fetch = [&](const int4 &x) {
+        e = make_int4(__builtin_amdgcn_readfirstlane(x.x), __builtin_amdgcn_readfirstlane(x.y),
+                      __builtin_amdgcn_readfirstlane(x.z), __builtin_amdgcn_readfirstlane(x.w));
+        const int2 w = I.sp_var[(size_t)e.x * kChunk + lane];
+        lw = w.x;
+        kk = (uint32_t)w.y;
+#pragma unroll
+        for (int i = 0; i < PRE; ++i)
+            q[i] = rp(e.z + i);
+    };
+    __syncthreads();
+    if (items)
+        fetch(list[0]);
+    const bool first = (lane & ((1 << LG) - 1)) < 4;  // the quad that decides
+    uint32_t n_acc = 0;
+    for (int s = 0; s < C.n_sweeps; ++s) {
+        const uint32_t t = C.t0 + (uint32_t)s;
+        const uint32_t *T = tl + (s & 1) * tab_words;
+        // the next sweep's thresholds, stored at the end of this one
+        uint32_t tn[2] = {0, 0};
+        const uint32_t *tg = tab + (size_t)(s + 1) * C.sweep_words;
+        const bool more = s + 1 < C.n_sweeps;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (more && tid + i * nthr < tab_words)
+                tn[i] = tg[tid + i * nthr];
+        int dsum = 0, cur = 0;
+        for (int it = 0; it < items; ++it) {
+            for (; cur < e.y; ++cur)
+                __syncthreads();
+            const int4 next = list[it + 1 < items ? it + 1 : 0];
+            if ((it & ((1 << LG) - 1)) == 0) {
+                // words of the wave's next 2^LG chunks, one variable per lane
+                const int k = min(it * PER + lane, items * PER - 1);
+                const uint32_t v = (uint32_t)vars[k];
+                issue_fence();
+                words[lane] = philox4x32_10(v, t, (uint32_t)g, kStreamKsatSweep, C.key0, C.key1);
+                issue_fence();
+            }
+            const int v = max(lw, 0);
+            const uint32_t xi = lds_load_u8((uint32_t)v);
+            const uint32_t cl = cls[v];
+            const uint32_t u =
+                reinterpret_cast<const uint32_t *>(words)[((it & ((1 << LG) - 1)) * PER + (lane >> LG)) * 4 + j];
+            uint32_t acc = kk;
+            // straight-line code per count, every gather issued before the
+            // first is used
+            auto walk = [&](auto np) {
+                constexpr int NP = decltype(np)::value < PRE ? decltype(np)::value : PRE;
+                uint32_t x[2 * NP][3], sm[2 * NP];
+#pragma unroll
+                for (int i = 0; i < NP; ++i) {
+                    slot_gather(make_uint2(q[i].x, q[i].y), x[2 * i], sm[2 * i]);
+                    slot_gather(make_uint2(q[i].z, q[i].w), x[2 * i + 1], sm[2 * i + 1]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < 2 * NP; ++i)
+                    acc -= spread4(x[i][0] | x[i][1] | x[i][2]) ^ sm[i];
+            };
+            using std::integral_constant;
+            switch (min(e.w, PRE)) {
+            case 1: walk(integral_constant<int, 1>{}); break;
+            case 2: walk(integral_constant<int, 2>{}); break;
+            case 3: walk(integral_constant<int, 3>{}); break;
+            case 4: walk(integral_constant<int, 4>{}); break;
+            case 5: walk(integral_constant<int, 5>{}); break;
+            default: walk(integral_constant<int, PRE>{});
+            }
+            for (int k = PRE; k < e.w; ++k) {
+                const uint4 r = rp(e.z + k);
+                acc = acc - slot_step(0u, make_uint2(r.x, r.y)) - slot_step(0u, make_uint2(r.z, r.w));
+            }
+            const bool live = lw >= 0 && first && j < nact;
+            // the next chunk's records (the first chunk's after the last: the
+            // next sweep starts with it)
+            fetch(next);
+            issue_fence();
+            acc = lane_group_sum(acc, LG);
+            const int S = (int)((acc >> (8 * j)) & 0xFFu) - 128;
+            const int de = ((xi >> j) & 1u) ? S : -S;
+            const uint32_t thr = T[cl + max(de, 0)];
+            const bool take = live & ((de <= 0) | (u < thr));
+            uint32_t flip = take ? 1u << j : 0u;
+            flip |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)flip, 0xB1, 0xF, 0xF, false);
+            flip |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)flip, 0x4E, 0xF, 0xF, false);
+            dsum += take ? de : 0;
+            n_acc += take;
+            if (flip && live && j == 0) {
+                const uint32_t nx = xi ^ flip;
+                lds_store_u8((uint32_t)v, nx);
+                lds_store_u8((uint32_t)(n + v), ~nx & amask);
+            }
+        }
+        for (; cur < I.n_colors; ++cur)
+            __syncthreads();
+        // sweep end: this wave's energy changes by replica, then one barrier
+        dsum += __shfl_xor(dsum, 4, 64);
+        dsum += __shfl_xor(dsum, 8, 64);
+        dsum += __shfl_xor(dsum, 16, 64);
+        dsum += __shfl_xor(dsum, 32, 64);
+        int *rs = red + 4 * (s & 1);
+        if (lane < kGroup && dsum)
+            atomicAdd(&rs[lane], dsum);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (more && tid + i * nthr < tab_words)
+                tl[((s + 1) & 1) * tab_words + tid + i * nthr] = tn[i];
+        for (int i = tid + 2 * nthr; more && i < tab_words; i += nthr)
+            tl[((s + 1) & 1) * tab_words + i] = tg[i];
+        __syncthreads();
+        // every wave keeps the replicas' energies; the sums of the sweep
+        // before last are cleared for the next one
+        E += rs[j];
+        if (tid < kGroup)
+            red[4 * ((s + 1) & 1) + tid] = 0;
+        const bool imp = j < nact && E < best;
+        best = imp ? E : best;
+        if (j < nact && fh < 0 && E <= C.target)
+            fh = (int)(t + 1);
+        const uint32_t im = (uint32_t)__ballot(imp) & 0xFu;
+        if (im) {  // (the same in every wave)
+            for (int v = tid; v < n; v += nthr)
+                bx[v] = (uint8_t)((bx[v] & ~im) | (xt[v] & im));
+            __syncthreads();
+        }
+    }
+    __syncthreads();
+    for (int v = tid; v < n; v += nthr) {
+        xg[v] = xt[v];
+        bg[v] = bx[v];
+    }
+    if (tid < nact) {
+        R.energy[r0 + tid] = E;
+        R.best[r0 + tid] = best;
+        R.first_hit[r0 + tid] = fh;
+    }
+    unsigned long long acc_w = n_acc;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+        acc_w += __shfl_xor(acc_w, off, 64);
+    if (lane == 0 && acc_w)
+        atomicAdd(R.accepted, acc_w);
+}
+
 // One item (GPW groups of 4 replicas) per workgroup (item = blockIdx.x).
 template <int GPW>
 __global__ void __launch_bounds__(1024) ksat_sweep_kernel(KsatDev I, KsatRepDev R, SweepCall C) {
     extern __shared__ __align__(16) uint8_t smem[];
     sweep_group<GPW>(I, R, C, blockIdx.x, smem);
-}
-
-// The same with the instance staged in LDS (one group of 4 replicas per
-// workgroup).
-__global__ void __launch_bounds__(1024) ksat_sweep_staged_kernel(KsatDev I, KsatRepDev R, SweepCall C) {
-    extern __shared__ __align__(16) uint8_t smem[];
-    sweep_group<1, true>(I, R, C, blockIdx.x, smem);
 }
 
 // Batched launch: many replica sets (jobs) of different instances in one
@@ -737,20 +959,6 @@ size_t ksat_sweep_lds_bytes(int n, int n_classes, int stride) {
     return align_up(2 * (size_t)n + 2, 16) + align_up((size_t)n_classes * stride, 4) * 4 + 16 * sizeof(int);
 }
 
-// LDS of the staged instance (records, chunk descriptors, lane words, class
-// ranges, the sweep's random words per variable), placed after the block above
-static size_t ksat_staged_bytes(const KsatDev &I) {
-    return align_up(I.rec_bytes, 16) + align_up((size_t)I.n_chunks * 8, 16) + (size_t)I.n_chunks * kChunk * 4 +
-           align_up(((size_t)I.n_colors + 1) * 4, 16) + (size_t)I.n * 16;
-}
-
-// small instances take the staged kernel unless NMC_KSAT_STAGE=0 (read at
-// every launch, so a process can compare the two)
-static bool ksat_stage_enabled() {
-    const char *e = std::getenv("NMC_KSAT_STAGE");
-    return !(e && e[0] == '0');
-}
-
 hipError_t launch_set_status(const SetStatusSrc *src, SetStatus *out, int n_sets, hipStream_t s) {
     hipLaunchKernelGGL(set_status_kernel, dim3(n_sets), dim3(256), 0, s, src, out);
     return hipGetLastError();
@@ -799,15 +1007,28 @@ hipError_t ksat_launch_sweep(const KsatDev &I, const KsatRepDev &R, const SweepC
     }();
     if (attr != hipSuccess)
         return attr;
-    static const hipError_t attr_staged = hipFuncSetAttribute(
-        (const void *)ksat_sweep_staged_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
-    if (attr_staged != hipSuccess)
-        return attr_staged;
-    const size_t staged = lds + ksat_staged_bytes(I);
+    static const hipError_t attr_split = [] {
+        hipError_t e = hipSuccess;
+        for (const void *f : {(const void *)ksat_split_kernel<2>, (const void *)ksat_split_kernel<3>,
+                              (const void *)ksat_split_kernel<4>})
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
+        return e;
+    }();
+    if (attr_split != hipSuccess)
+        return attr_split;
+    const size_t split =
+        I.sp_lg ? split_lds(I.n, I.n_colors, I.sp_chunks, I.sp_lg, C.n_classes * C.stride, I.sp_waves).total : 0;
     if (C.gpw == 2)
         hipLaunchKernelGGL(ksat_sweep_kernel<2>, dim3((R.n_groups + 1) / 2), dim3(block_threads), lds, s, I, R, C);
-    else if (staged <= kLdsBytes && ksat_stage_enabled())
-        hipLaunchKernelGGL(ksat_sweep_staged_kernel, dim3(R.n_groups), dim3(block_threads), staged, s, I, R, C);
+    // (also with more groups than CUs: 4096 replicas of n = 200, 1000, 5000, 9000
+    // take 19, 56, 191, 255 us per sweep against 132, 304, 416, 420; a set tuned
+    // to smaller workgroups keeps them)
+    else if (split && split <= kLdsBytes && block_threads == 1024)
+        hipLaunchKernelGGL(I.sp_lg == 2   ? ksat_split_kernel<2>
+                           : I.sp_lg == 3 ? ksat_split_kernel<3>
+                                          : ksat_split_kernel<4>,
+                           dim3(R.n_groups), dim3(64 * I.sp_waves), split, s, I, R, C);
     else
         hipLaunchKernelGGL(ksat_sweep_kernel<1>, dim3(R.n_groups), dim3(block_threads), lds, s, I, R, C);
     return hipGetLastError();

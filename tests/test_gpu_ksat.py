@@ -313,3 +313,32 @@ def test_eight_replicas_per_workgroup_full_size():
         assert (x[lo:hi] == orep.x[lo:hi]).all()
         assert (be["energy"][lo:hi] == orep.energy[lo:hi]).all()
         assert (be["first_hit"][lo:hi] == orep.first_hit[lo:hi]).all()
+
+
+@pytest.mark.parametrize("n,k,alpha,R,cap", [(1, 1, "1", 5, 0), (5, 2, "2", 3, 0), (200, 4, "9.6", 66, 0),
+                                             (333, 4, "9.8", 37, 0), (400, 4, "22", 8, 0), (700, 4, "9.5", 8, 1),
+                                             (1203, 3, "4.15", 130, 0), (2500, 4, "9.8", 33, 100),
+                                             (5000, 4, "9.884", 9, 0), (9001, 4, "9.9", 6, 0)])
+def test_split_sweeps(n, k, alpha, R, cap):
+    """Split sweeps (several lanes per variable, one replica decided per lane):
+    4, 8 and 16 lanes per variable, more record pairs than are loaded ahead
+    (n = 400, degree over 100), more chunks per class than waves, one variable
+    per class, ragged replica counts, three host classes with beta = 0 and 60,
+    calls of one and of no sweep; integer results, so exact."""
+    say(f"case: split n={n} k={k} R={R}")
+    cp, lits = instances.gen_ksat(n, alpha, k, n)
+    p = KsatPair(n, cp, lits, R, n + 1, cap)
+    p.anneal(instances.linear_schedule(0.1, 4.0, 17)[None, :], target=3)
+    p.compare()
+    cls = p.backbone(1, 2, n > 5)
+    p.anneal(instances.profile_schedule(np.full(6, 4.0), instances.linear_schedule(0.5, 4.0, 6)), profile="backbone",
+             class_of=cls)
+    p.compare()
+    host = (np.arange(n) % 3).astype(np.uint8)
+    p.anneal(np.stack([np.full(4, 3.0), np.zeros(4), np.full(4, 60.0)]), class_of=host,
+             target=int(p.orep.best.min()))
+    p.compare()
+    p.anneal(np.zeros((1, 0)), target=10**6)
+    p.compare()
+    p.anneal(np.full((1, 1), 2.0))
+    p.compare()
