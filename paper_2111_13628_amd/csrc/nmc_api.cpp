@@ -937,7 +937,7 @@ struct nmc_replicas {
     unsigned long long *pt_acc = nullptr;
     // LBP workspace (library-owned, sized for the instance on first use)
     uint8_t *lbp_dev = nullptr;
-    int64_t *lbp_pin = nullptr;  // pinned host words for the per-batch readback
+    double *lbp_pin = nullptr;  // pinned host words the step ends are written to
     // whitening workspace (library-owned): white bits, counts, passes
     uint8_t *wh_dev = nullptr;
     // LBP message-iteration kernel time (profiling)
@@ -1961,6 +1961,7 @@ static int lbp_workspace(LbpRun &r, hipStream_t s) {
     W.scal = reinterpret_cast<unsigned long long *>(b + o_scal);
     W.res = reinterpret_cast<double *>(b + o_res);
     W.ctl = reinterpret_cast<int32_t *>(b + o_ctl);
+    W.status = P->lbp_pin;
     W.label = reinterpret_cast<int32_t *>(b + o_lab);
     W.out_label = reinterpret_cast<int32_t *>(b + o_olab);
     W.size = reinterpret_cast<int32_t *>(b + o_size);
@@ -1990,7 +1991,7 @@ static size_t lbp_job_offset(const nmc_instance *I) {
 // lambda steps (all runs share the configuration, so the runs still going
 // share lambda); jobs_dev holds the runs' job descriptors on the device.
 static int lbp_run_all(std::vector<LbpRun> &runs, const LbpJob *jobs_dev, const LbpDims &D, const nmc_lbp_config &c,
-                       int64_t *pin, hipStream_t s, bool profiling, double *prof_ms, int64_t *prof_iters) {
+                       double *pin, hipStream_t s, bool profiling, double *prof_ms, int64_t *prof_iters) {
     const double w = 1.0 - std::exp(-2.0 * c.beta);
     const size_t nr = runs.size();
     hipEvent_t pe[2] = {nullptr, nullptr};
@@ -2011,33 +2012,30 @@ static int lbp_run_all(std::vector<LbpRun> &runs, const LbpJob *jobs_dev, const 
         if (r.ubytes)
             HIP_OR_FAIL(hipMemsetAsync(r.W.u, 0, r.ubytes, s));
     HIP_OR_FAIL(lbp_launch_setup(jobs_dev, D, c.lambda0, s));
-    HIP_OR_FAIL(lbp_launch_clause(jobs_dev, D, w, 0, s));
+    HIP_OR_FAIL(lbp_launch_first(jobs_dev, D, w, s));
     double lambda = c.lambda0;
+    int32_t guess = 8;  // iterations queued at once: what the last step took
     for (;;) {
-        // one step for the runs still going: queued in batches of 8, then
-        // 16 iterations; convergence is decided on the device after every
-        // iteration and read back (pinned memory) once per batch
-        for (auto &r : runs)
-            if (!r.done) {
-                if (r.ubytes)
-                    HIP_OR_FAIL(hipMemcpyAsync(r.keep, r.W.u, r.ubytes, hipMemcpyDeviceToDevice, s));
-                HIP_OR_FAIL(hipMemsetAsync(r.W.scal, 0, 2 * kLbpDeltaSlots * 8, s));
-                HIP_OR_FAIL(hipMemsetAsync(r.W.ctl, 0, 8, s));
+        // one step for the runs still going: queued in batches (convergence
+        // is decided on the device after every iteration; the outcome of a
+        // stopped step arrives in pinned memory)
+        for (size_t k = 0; k < nr; ++k)
+            if (!runs[k].done) {
+                HIP_OR_FAIL(lbp_launch_begin(runs[k].W, runs[k].keep, runs[k].ubytes / 8, s));
+                pin[4 * k] = 0.0;
             }
         int32_t queued = 0;
         for (;;) {
-            const int32_t cnt = std::min(queued ? 16 : 8, c.max_iter - queued);
+            const int32_t cnt = std::min(queued ? 8 : guess, c.max_iter - queued);
             if (pe[0])
                 HIP_OR_FAIL(hipEventRecord(pe[0], s));
             HIP_OR_FAIL(lbp_launch_iterations(jobs_dev, D, lambda, w, c.tol, c.max_iter, queued, cnt, s));
             if (pe[1])
                 HIP_OR_FAIL(hipEventRecord(pe[1], s));
             queued += cnt;
-            for (size_t k = 0; k < nr; ++k)
-                if (!runs[k].done) {
-                    HIP_OR_FAIL(hipMemcpyAsync(pin + 2 * k, runs[k].W.ctl, 8, hipMemcpyDeviceToHost, s));
-                    HIP_OR_FAIL(hipMemcpyAsync(pin + 2 * k + 1, runs[k].W.res + 2, 8, hipMemcpyDeviceToHost, s));
-                }
+            // (runs that stopped earlier only overwrite scratch that the
+            // final pass recomputes)
+            HIP_OR_FAIL(lbp_launch_step_end(jobs_dev, D, lambda, c.tol, c.max_iter, queued - 1, s));
             HIP_OR_FAIL(hipStreamSynchronize(s));
             if (pe[0]) {
                 float ms = 0;
@@ -2046,32 +2044,22 @@ static int lbp_run_all(std::vector<LbpRun> &runs, const LbpJob *jobs_dev, const 
             }
             bool all_stopped = true;
             for (size_t k = 0; k < nr; ++k)
-                if (!runs[k].done && reinterpret_cast<const int32_t *>(pin + 2 * k)[0] == 0)
+                if (!runs[k].done && pin[4 * k] == 0.0)
                     all_stopped = false;
             if (all_stopped || queued >= c.max_iter)
                 break;
         }
-        // overlaps at this lambda (every run; the ones that stopped earlier
-        // only overwrite scratch that the final pass recomputes)
-        HIP_OR_FAIL(lbp_launch_var(jobs_dev, D, lambda, 1, s));
-        HIP_OR_FAIL(lbp_launch_overlap(jobs_dev, D, s));
-        std::vector<double> pov(nr, 0.0);
+        std::vector<double> pov(nr, 0.0), delta(nr, 0.0);
         std::vector<int32_t> ctl0(nr, 0), ctl1(nr, 0);
-        std::vector<double> delta(nr, 0.0);
+        guess = 1;
         for (size_t k = 0; k < nr; ++k)
             if (!runs[k].done) {
-                const int32_t *cw = reinterpret_cast<const int32_t *>(pin + 2 * k);
-                ctl0[k] = cw[0];
-                ctl1[k] = cw[1];
-                std::memcpy(&delta[k], pin + 2 * k + 1, 8);
+                ctl0[k] = (int32_t)pin[4 * k];
+                ctl1[k] = (int32_t)pin[4 * k + 1];
+                delta[k] = pin[4 * k + 2];
+                pov[k] = pin[4 * k + 3];
+                guess = std::max(guess, ctl1[k] + 1);
             }
-        for (size_t k = 0; k < nr; ++k)
-            if (!runs[k].done)
-                HIP_OR_FAIL(hipMemcpyAsync(pin + 2 * k, runs[k].W.res, 8, hipMemcpyDeviceToHost, s));
-        HIP_OR_FAIL(hipStreamSynchronize(s));
-        for (size_t k = 0; k < nr; ++k)
-            if (!runs[k].done)
-                std::memcpy(&pov[k], pin + 2 * k, 8);
         bool any = false;
         for (size_t k = 0; k < nr; ++k) {
             LbpRun &r = runs[k];
@@ -2109,7 +2097,7 @@ static int lbp_run_all(std::vector<LbpRun> &runs, const LbpJob *jobs_dev, const 
         HIP_OR_FAIL(lbp_launch_var(jobs_dev + k, one, runs[k].have ? runs[k].kept_lambda : c.lambda0, 1, s));
     }
     HIP_OR_FAIL(lbp_launch_overlap(jobs_dev, D, s));
-    HIP_OR_FAIL(lbp_launch_clause(jobs_dev, D, w, 1, s));
+    HIP_OR_FAIL(lbp_launch_moment(jobs_dev, D, w, s));
     // connected components of the rigid clauses (one shared change flag)
     HIP_OR_FAIL(lbp_launch_label_init(jobs_dev, D, s));
     int32_t *flag = runs[0].W.flag;
@@ -2188,18 +2176,15 @@ static int lbp_impl(nmc_replicas *P, int32_t replica, int32_t which, const nmc_l
         HIP_OR_FAIL(hipMemcpyAsync(class_out, P->k.cls, n, hipMemcpyDeviceToHost, s));
     if (mag_out && n)
         HIP_OR_FAIL(hipMemcpyAsync(mag_out, runs[0].W.mag, (size_t)n * 8, hipMemcpyDeviceToHost, s));
-    // the moments are in the LBP clause order on the device
-    std::vector<double> corr_lbp;
+    // the moments are in the LBP clause order on the device: put in the
+    // caller's order in the saved messages' place, which the run is done with
     if (corr_out && m) {
-        corr_lbp.resize(m);
-        HIP_OR_FAIL(hipMemcpyAsync(corr_lbp.data(), runs[0].W.corr, (size_t)m * 8, hipMemcpyDeviceToHost, s));
+        HIP_OR_FAIL(lbp_launch_corr_out(I->ksat_dev(), runs[0].W.corr, runs[0].keep, s));
+        HIP_OR_FAIL(hipMemcpyAsync(corr_out, runs[0].keep, (size_t)m * 8, hipMemcpyDeviceToHost, s));
     }
     if (label_out && n)
         HIP_OR_FAIL(hipMemcpyAsync(label_out, runs[0].W.out_label, (size_t)n * 4, hipMemcpyDeviceToHost, s));
     HIP_OR_FAIL(hipStreamSynchronize(s));
-    if (corr_out && m)
-        for (int32_t a = 0; a < m; ++a)
-            corr_out[a] = corr_lbp[I->lbp_pos[a]];
     if (res)
         lbp_fill_result(runs[0], *cfg, res);
     return ok();
@@ -2489,7 +2474,7 @@ struct nmc_batch {
     double prof_attempts = 0;
     // batched LBP: job descriptors (device) and control readback (pinned)
     LbpJob *lbp_jobs = nullptr;
-    int64_t *lbp_pin = nullptr;
+    double *lbp_pin = nullptr;
     size_t lbp_cap = 0;
     double lbp_ms = 0;
     int64_t lbp_iters = 0;
@@ -3398,7 +3383,7 @@ int nmc_batch_lbp_backbone(nmc_batch *B, const int32_t *replicas, int32_t which,
             }
             B->lbp_cap = 0;
             HIP_OR_FAIL(hipMalloc(reinterpret_cast<void **>(&B->lbp_jobs), ns * sizeof(LbpJob)));
-            HIP_OR_FAIL(hipHostMalloc(reinterpret_cast<void **>(&B->lbp_pin), std::max<size_t>(2 * ns, 8) * 8,
+            HIP_OR_FAIL(hipHostMalloc(reinterpret_cast<void **>(&B->lbp_pin), 4 * ns * sizeof(double),
                                       hipHostMallocDefault));
             B->lbp_cap = ns;
         }
@@ -3415,6 +3400,7 @@ int nmc_batch_lbp_backbone(nmc_batch *B, const int32_t *replicas, int32_t which,
             J.I = P->inst->ksat_dev();
             J.W = runs[k].W;
             J.W.flag = runs[0].W.flag;  // one change flag for the whole batch
+            J.W.status = B->lbp_pin + 4 * k;
             J.xs_row = (which == NMC_STATE_BEST ? P->k.best_xs : P->k.xs) + (size_t)(replicas[k] / kGroup) * P->inst->n;
             J.bit = replicas[k] % kGroup;
             J.cls = P->k.cls;

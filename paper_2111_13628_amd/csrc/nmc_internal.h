@@ -318,6 +318,7 @@ struct LbpWork {
     unsigned long long *scal;    // [2][64] bits of the largest |du| of an iteration, by parity and slot
     double *res;                 // [0] overlap p, [1] self-overlap q1, [2] last iteration's max |du|
     int32_t *ctl;                // [0] 0 running / 1 converged / 2 out of iterations, [1] iterations
+    double *status;              // [4] pinned host words: a stopped step's ctl[0], ctl[1], res[2], res[0]
     int32_t *label, *out_label, *size;  // [N]
     uint8_t *seeded;             // [N]
     int32_t *flag;               // [1] labels changed
@@ -344,11 +345,16 @@ struct LbpJudge {
 };
 hipError_t lbp_launch_setup(const LbpJob *jobs, const LbpDims &D, double lambda0, hipStream_t s);
 hipError_t lbp_launch_var(const LbpJob *jobs, const LbpDims &D, double lambda, int final_pass, hipStream_t s);
-hipError_t lbp_launch_clause(const LbpJob *jobs, const LbpDims &D, double w, int final_pass, hipStream_t s);
-// gated iterations first .. first + count - 1 of one step (variable side with
-// the previous iteration's control, clause side; control after the last)
+// the first messages (u = 0, T = H)
+hipError_t lbp_launch_first(const LbpJob *jobs, const LbpDims &D, double w, hipStream_t s);
+hipError_t lbp_launch_moment(const LbpJob *jobs, const LbpDims &D, double w, hipStream_t s);
+hipError_t lbp_launch_begin(const LbpWork &W, double *keep, size_t n_words, hipStream_t s);
+hipError_t lbp_launch_corr_out(const KsatDev &I, const double *corr, double *out, hipStream_t s);
+// gated iterations first .. first + count - 1 of one step
 hipError_t lbp_launch_iterations(const LbpJob *jobs, const LbpDims &D, double lambda, double w, double tol,
                                  int max_iter, int first, int count, hipStream_t s);
+hipError_t lbp_launch_step_end(const LbpJob *jobs, const LbpDims &D, double lambda, double tol, int max_iter, int last,
+                               hipStream_t s);
 hipError_t lbp_launch_overlap(const LbpJob *jobs, const LbpDims &D, hipStream_t s);
 hipError_t lbp_launch_label_init(const LbpJob *jobs, const LbpDims &D, hipStream_t s);
 hipError_t lbp_launch_hook_jump(const LbpJob *jobs, const LbpDims &D, double cut, hipStream_t s);

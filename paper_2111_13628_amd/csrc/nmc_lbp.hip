@@ -19,7 +19,7 @@
 //   h_{i->a} = sigma_{ia} T_i - u_{a->i}                         (the cavity field)
 //   u_{a->i} = -1/2 ln[1 - (1 - e^{-2 beta}) prod_{j in da \ i} (1 - tanh h_{j->a}) / 2]
 // The variable kernel (sixteen lanes per variable) writes only T, N doubles
-// that stay in L2; the clause kernel (one thread per clause) forms each h
+// that stay in L2; the clause kernel (one lane per edge) forms each h
 // from T and its own u, so no per-edge h is stored.  Each message is kept
 // twice: clause-major (u, the clause kernel's own contiguous reads and
 // writes) and variable-major with its sign applied (sigma u at the edge's
@@ -33,8 +33,11 @@
 // iteration k converged (every wave reads the 64 slots; one thread records
 // the decision and clears the other set for the coming clause pass), and
 // once stopped the kernels of the rest of the batch return at once, so the
-// result is that of checking after every iteration.  A one-thread kernel
-// decides on the batch's last iteration.  Everything is fp64 (8 bytes per
+// result is that of checking after every iteration.  The batch ends with a
+// variable pass that decides on the last iteration in the same way and, once
+// the step has stopped, forms the marginals for the overlaps, which one more
+// kernel sums and writes to pinned host words: one synchronization per batch.
+// Everything is fp64 (8 bytes per
 // edge and message).
 //
 // Components: labels start as the variable's index; every rigid clause
@@ -42,6 +45,7 @@
 // (atomicMin), then labels jump to their label's label, until nothing
 // changes.  The fixed point gives every variable of a component the
 // component's smallest index.
+#include <algorithm>
 #include <cmath>
 
 #include "nmc_internal.h"
@@ -100,10 +104,12 @@ __global__ void lbp_setup_kernel(const LbpJob *jobs, double lambda0) {
 // variable side: T_i; with final != 0 also <r_i> = tanh T_i.  kVarLanes
 // lanes share a variable: each takes every kVarLanes-th incidence
 // (consecutive lanes read consecutive variable-major messages), the partial
-// sums meet by butterfly shuffles inside the lane group.  With gated != 0
-// the launch does nothing once the iteration control has stopped; with
-// G.judge >= 0 it first decides on the previous iteration (see above) and
-// returns without writing T if that iteration ended the step.
+// sums meet by butterfly shuffles inside the lane group.  With gated = 1 (an
+// iteration of a step) the launch does nothing once the iteration control
+// has stopped; with G.judge >= 0 it first decides on the previous iteration
+// (see above) and returns without writing T if that iteration ended the
+// step.  With gated = 2 (the end of a queued batch) it decides on the batch's
+// last iteration in the same way and runs only if the step has stopped.
 constexpr int kVarLanes = 16;
 constexpr int kDeltaSlots = kLbpDeltaSlots;
 constexpr int kVarRound = 4;
@@ -116,9 +122,10 @@ __global__ void lbp_var_kernel(const LbpJob *jobs, double lambda, int final_pass
     const LbpJob &J = jobs[blockIdx.y];
     const KsatDev &I = J.I;
     const LbpWork &W = J.W;
-    if (gated && W.ctl[0])
+    const int stopped = gated ? W.ctl[0] : 0;
+    if (gated == 1 && stopped)
         return;
-    if (G.judge >= 0) {
+    if (G.judge >= 0 && !stopped) {
         // the previous iteration's largest |du|: its slots, dealt to the lanes
         unsigned long long mx = 0;
         for (int k = threadIdx.x & 63; k < kDeltaSlots; k += 64) {
@@ -136,7 +143,7 @@ __global__ void lbp_var_kernel(const LbpJob *jobs, double lambda, int final_pass
             W.ctl[1] = G.iters;
             W.ctl[0] = stop;
         }
-        if (stop)
+        if ((gated == 1) == (stop != 0))
             return;
     }
     if (G.clear >= 0 && blockIdx.x == 0)
@@ -174,125 +181,158 @@ __global__ void lbp_var_kernel(const LbpJob *jobs, double lambda, int final_pass
         W.mag[i] = tanh(tot);
 }
 
-// iteration control at the end of a batch, one thread: the batch's last
-// iteration's largest |du| (its set of 64 slots), the iteration count, and
-// stop on convergence (ctl[0] = 1) or at max_iter (ctl[0] = 2)
-__global__ void lbp_judge_kernel(const LbpJob *jobs, LbpJudge G) {
-    const LbpWork &W = jobs[blockIdx.y].W;
-    if (W.ctl[0])
-        return;
-    unsigned long long mx = 0;
-    for (int k = 0; k < kDeltaSlots; ++k) {
-        const unsigned long long v = W.scal[G.judge * kDeltaSlots + k];
-        mx = v > mx ? v : mx;
-    }
-    const double d = __longlong_as_double((long long)mx);
-    W.res[2] = d;
-    W.ctl[1] = G.iters;
-    W.ctl[0] = lbp_decide(d, G);
+// v of the lane with the two lowest lane bits changed as the quad permutation
+// CTRL says (0xB1: lane ^ 1, 0x4E: lane ^ 2).
+template <int CTRL>
+__device__ __forceinline__ double quad_get(double v) {
+    const long long x = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(x >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// clause side: h_{j->a} = sigma_j T_{v_j} - u_{a->j}, then the new u for
-// every edge of a and the largest change; with final != 0 the clause moment
-// instead (u unchanged)
-__global__ void __launch_bounds__(256) lbp_clause_kernel(const LbpJob *jobs, double w, int final_pass, int gated,
-                                                         int set) {
+// ln(1 - x) for 0 <= x <= 1, from 1 + f = 1 - x or, away from 1, from the
+// mantissa of 1 - x in [1/sqrt 2, sqrt 2): ln(1 + f) = 2 atanh(s), s = f / (2 +
+// f), |s| < 0.172, by the series of atanh to s^21 (the first term left out is
+// below 2^-57 of the sum).  With f = -x exact while x < 1 - 1/sqrt 2, small x
+// lose nothing to the subtraction.
+__device__ __forceinline__ double log_1m(double x) {
+    const double y = 1.0 - x;
+    double m = __builtin_amdgcn_frexp_mant(y);  // [1/2, 1)
+    int k = __builtin_amdgcn_frexp_exp(y);
+    const bool low = m < 0.70710678118654752;
+    m = low ? 2.0 * m : m;
+    k = low ? k - 1 : k;
+    const double num = k == 0 ? -x : m - 1.0, den = k == 0 ? 2.0 - x : m + 1.0;
+    double r = __builtin_amdgcn_rcp(den);
+    r = fma(fma(-den, r, 1.0), r, r);
+    r = fma(fma(-den, r, 1.0), r, r);
+    double s = num * r;
+    s = fma(fma(-den, s, num), r, s);
+    const double z = s * s;
+    double p = 1.0 / 21.0;
+    p = fma(p, z, 1.0 / 19.0);
+    p = fma(p, z, 1.0 / 17.0);
+    p = fma(p, z, 1.0 / 15.0);
+    p = fma(p, z, 1.0 / 13.0);
+    p = fma(p, z, 1.0 / 11.0);
+    p = fma(p, z, 1.0 / 9.0);
+    p = fma(p, z, 1.0 / 7.0);
+    p = fma(p, z, 1.0 / 5.0);
+    p = fma(p, z, 1.0 / 3.0);
+    const double s2 = 2.0 * s;
+    const double l = fma((double)k, 0.69314718055994531, fma(s2 * z, p, s2));
+    return y > 0.0 ? l : (y == 0.0 ? -INFINITY : NAN);
+}
+
+// One message iteration, clause side, one lane per edge e = 4a + j (a clause
+// is a quad): h = sigma_j T_{v_j} - u, P = (1 - tanh h) / 2 = 1 / (1 + e^{2h})
+// (which keeps its relative accuracy where tanh h rounds to 1), the product of
+// the clause's other P by quad permutations, the new u and the largest
+// change.  Every load and store but the gather of T and the variable-major
+// copy is contiguous.  A small instance is bound by the chain of one lane's
+// exp, reciprocal and logarithm, which a thread per clause ran four times in
+// turn: at 19 800 clauses 8.2 -> 4.6 us, at 79 200 12.2 -> 8.4 us.  A large one
+// is bound by the variable-major stores, whose lines every die writes in
+// part (24 us without them): at 495 000 clauses 32.3 -> 30.3 us for 63 MB.
+// Four edges to a lane gave the same, stores past the L2 50 us.
+__global__ void __launch_bounds__(256) lbp_edge_kernel(const LbpJob *jobs, double w, int gated, int set) {
     const LbpJob &J = jobs[blockIdx.y];
     const KsatDev &I = J.I;
     const LbpWork &W = J.W;
     if (gated && W.ctl[0])
         return;
     __shared__ double wmax[256 / 64];
-    const int a = blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const uint32_t n = (uint32_t)I.n;
     double dmax = 0.0;
-    if (a < I.m) {
-        // the clause's four addresses and messages as vector loads, then the
-        // four field totals together (a padding slot reads T_0 and drops it)
-        const uint4 ad = *reinterpret_cast<const uint4 *>(I.lbp_caddr + (size_t)a * 4);
-        double2 *up = reinterpret_cast<double2 *>(W.u + (size_t)a * 4);
-        const double2 u01 = up[0], u23 = up[1];
-        const uint32_t av[4] = {ad.x, ad.y, ad.z, ad.w};
-        const double uo[4] = {u01.x, u01.y, u23.x, u23.y};
-        int k = 4;
-#pragma unroll
-        for (int j = 3; j >= 0; --j)
-            if (av[j] >= 2u * (uint32_t)I.n)
-                k = j;
-        int vj[4];
-        double sg[4], tv[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const bool neg = av[j] >= (uint32_t)I.n;
-            vj[j] = j < k ? (int)(neg ? av[j] - (uint32_t)I.n : av[j]) : 0;
-            sg[j] = neg ? -1.0 : 1.0;
+    if (e < (size_t)4 * I.m) {  // (whole quads)
+        // (an address from 2 n on is a padding slot: it drops out of the product)
+        const uint32_t ad = I.lbp_caddr[e];
+        const double uo = W.u[e];
+        const int ep = W.epos[e];
+        const bool in = ad < 2u * n, neg = ad >= n;
+        double P = 1.0;
+        if (in) {
+            const double tv = W.T[neg ? ad - n : ad];
+            const double h = (neg ? -tv : tv) - uo;
+            P = 1.0 / (1.0 + exp(2.0 * h));
         }
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            tv[j] = W.T[vj[j]];
-        double P[4], t[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (j < k) {
-                t[j] = tanh(sg[j] * tv[j] - uo[j]);
-                P[j] = (1.0 - t[j]) / 2.0;
-            }
-        if (!final_pass) {
-            double un[4] = {uo[0], uo[1], uo[2], uo[3]};
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (j < k) {
-                    double prod = 1.0;
-#pragma unroll
-                    for (int l = 0; l < 4; ++l)
-                        if (l < k && l != j)
-                            prod *= P[l];
-                    un[j] = -0.5 * log(1.0 - w * prod);
-                    const double d = fabs(un[j] - uo[j]);
-                    dmax = d > dmax ? d : dmax;
-                }
-            up[0] = make_double2(un[0], un[1]);
-            up[1] = make_double2(un[2], un[3]);
-            // the variable-major copies, sign applied (exact)
-            const int4 ep = *reinterpret_cast<const int4 *>(W.epos + (size_t)a * 4);
-            const int epv[4] = {ep.x, ep.y, ep.z, ep.w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (j < k)
-                    W.uv[epv[j]] = sg[j] * un[j];
-        } else {
-            double sat = 1.0, viol = 1.0, pv = 1.0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (j < k) {
-                    sat *= sg[j] * t[j];
-                    viol *= -sg[j] * P[j];
-                    pv *= P[j];
-                }
-            W.corr[a] = (sat - w * viol) / (1.0 - w * pv);
+        const double p1 = quad_get<0xB1>(P);
+        const double prod = p1 * quad_get<0x4E>(P * p1);
+        const double un = -0.5 * log_1m(w * prod);
+        if (in) {
+            dmax = fabs(un - uo);
+            W.u[e] = un;
+            // the variable-major copy, sign applied (exact)
+            W.uv[ep] = neg ? -un : un;
         }
     }
-    if (!final_pass) {
-        // wave max, workgroup max, one atomic per workgroup into a slot
-        for (int off = 32; off > 0; off >>= 1)
-            dmax = fmax(dmax, __shfl_xor(dmax, off));
-        if ((threadIdx.x & 63) == 0)
-            wmax[threadIdx.x >> 6] = dmax;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double m = wmax[0];
-            for (int k = 1; k < (int)(blockDim.x >> 6); ++k)
-                m = fmax(m, wmax[k]);
-            if (m > 0.0)
-                atomic_max_nonneg(&W.scal[set * kDeltaSlots + blockIdx.x % kDeltaSlots], m);
-        }
+    // wave max, workgroup max, one atomic per workgroup into a slot
+    for (int off = 32; off > 0; off >>= 1)
+        dmax = fmax(dmax, __shfl_xor(dmax, off));
+    if ((threadIdx.x & 63) == 0)
+        wmax[threadIdx.x >> 6] = dmax;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double m = wmax[0];
+        for (int k = 1; k < (int)(blockDim.x >> 6); ++k)
+            m = fmax(m, wmax[k]);
+        if (m > 0.0)
+            atomic_max_nonneg(&W.scal[set * kDeltaSlots + blockIdx.x % kDeltaSlots], m);
     }
 }
 
+// clause moments from the kept messages, one thread per clause
+__global__ void __launch_bounds__(256) lbp_moment_kernel(const LbpJob *jobs, double w) {
+    const LbpJob &J = jobs[blockIdx.y];
+    const KsatDev &I = J.I;
+    const LbpWork &W = J.W;
+    const int a = blockIdx.x * blockDim.x + threadIdx.x;
+    if (a >= I.m)
+        return;
+    double sat = 1.0, viol = 1.0, pv = 1.0;
+    for (int j = 0; j < 4; ++j) {
+        int v;
+        double sg;
+        if (!decode(I.lbp_caddr[(size_t)a * 4 + j], I.n, v, sg))
+            break;
+        const double t = tanh(sg * W.T[v] - W.u[(size_t)a * 4 + j]);
+        const double P = (1.0 - t) / 2.0;
+        sat *= sg * t;
+        viol *= -sg * P;
+        pv *= P;
+    }
+    W.corr[a] = (sat - w * viol) / (1.0 - w * pv);
+}
+
+// a step's start: the messages saved, the iteration control and the slots
+// cleared
+__global__ void __launch_bounds__(256) lbp_begin_kernel(LbpWork W, double *keep, int n_words) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    for (int i = t; i < n_words; i += gridDim.x * blockDim.x)
+        keep[i] = W.u[i];
+    if (t < 2 * kDeltaSlots)
+        W.scal[t] = 0ull;
+    if (t < 2)
+        W.ctl[t] = 0;
+}
+
+// clause moments in the caller's clause order
+__global__ void __launch_bounds__(256) lbp_corr_out_kernel(KsatDev I, const double *corr, double *out) {
+    const int a = blockIdx.x * blockDim.x + threadIdx.x;
+    if (a < I.m)
+        out[a] = corr[I.lbp_pos[a]];
+}
+
 // p = (1/N) sum s*_i <r_i> and q1 = (1/N) sum <r_i>^2 in a fixed order
-// (one workgroup: strided partial sums, then a tree)
-__global__ void __launch_bounds__(1024) lbp_overlap_kernel(const LbpJob *jobs) {
+// (one workgroup: strided partial sums, then a tree); gated: only once the
+// step has stopped, and the step's outcome then goes to the host's words
+__global__ void __launch_bounds__(1024) lbp_overlap_kernel(const LbpJob *jobs, int gated) {
     const KsatDev &I = jobs[blockIdx.y].I;
     const LbpWork &W = jobs[blockIdx.y].W;
+    if (gated && !W.ctl[0])
+        return;
     __shared__ double sp[1024], sq[1024];
     const int tid = threadIdx.x;
     double p = 0.0, q = 0.0;
@@ -314,6 +354,12 @@ __global__ void __launch_bounds__(1024) lbp_overlap_kernel(const LbpJob *jobs) {
     if (tid == 0) {
         W.res[0] = I.n ? sp[0] / I.n : 1.0;
         W.res[1] = I.n ? sq[0] / I.n : 1.0;
+        if (gated) {
+            W.status[0] = (double)W.ctl[0];
+            W.status[1] = (double)W.ctl[1];
+            W.status[2] = W.res[2];
+            W.status[3] = W.res[0];
+        }
     }
 }
 
@@ -441,7 +487,7 @@ int blocks(int n) { return (n + kLbpThreads - 1) / kLbpThreads; }
 }  // namespace
 
 // Every launcher covers a batch of jobs (grid y = job); blocks past a job's
-// own size return (the clause kernel only after its barriers).
+// own size return (the edge kernel only after its barriers).
 hipError_t lbp_launch_setup(const LbpJob *jobs, const LbpDims &D, double lambda0, hipStream_t s) {
     if (D.max_n > 0)
         hipLaunchKernelGGL(lbp_setup_kernel, dim3(blocks(D.max_n), D.n_jobs), dim3(kLbpThreads), 0, s, jobs, lambda0);
@@ -456,10 +502,28 @@ hipError_t lbp_launch_var(const LbpJob *jobs, const LbpDims &D, double lambda, i
     return hipGetLastError();
 }
 
-hipError_t lbp_launch_clause(const LbpJob *jobs, const LbpDims &D, double w, int final_pass, hipStream_t s) {
+hipError_t lbp_launch_first(const LbpJob *jobs, const LbpDims &D, double w, hipStream_t s) {
     if (D.max_m > 0)
-        hipLaunchKernelGGL(lbp_clause_kernel, dim3(blocks(D.max_m), D.n_jobs), dim3(kLbpThreads), 0, s, jobs, w,
-                           final_pass, 0, 0);
+        hipLaunchKernelGGL(lbp_edge_kernel, dim3(blocks(4 * D.max_m), D.n_jobs), dim3(kLbpThreads), 0, s, jobs, w, 0,
+                           0);
+    return hipGetLastError();
+}
+
+hipError_t lbp_launch_moment(const LbpJob *jobs, const LbpDims &D, double w, hipStream_t s) {
+    if (D.max_m > 0)
+        hipLaunchKernelGGL(lbp_moment_kernel, dim3(blocks(D.max_m), D.n_jobs), dim3(kLbpThreads), 0, s, jobs, w);
+    return hipGetLastError();
+}
+
+hipError_t lbp_launch_begin(const LbpWork &W, double *keep, size_t n_words, hipStream_t s) {
+    const int grid = (int)std::min<size_t>(std::max<size_t>((n_words + 255) / 256, 1), 2048);
+    hipLaunchKernelGGL(lbp_begin_kernel, dim3(grid), dim3(256), 0, s, W, keep, (int)n_words);
+    return hipGetLastError();
+}
+
+hipError_t lbp_launch_corr_out(const KsatDev &I, const double *corr, double *out, hipStream_t s) {
+    if (I.m > 0)
+        hipLaunchKernelGGL(lbp_corr_out_kernel, dim3(blocks(I.m)), dim3(kLbpThreads), 0, s, I, corr, out);
     return hipGetLastError();
 }
 
@@ -473,19 +537,27 @@ hipError_t lbp_launch_iterations(const LbpJob *jobs, const LbpDims &D, double la
             hipLaunchKernelGGL(lbp_var_kernel, dim3(blocks(D.max_n * kVarLanes), D.n_jobs), dim3(kLbpThreads), 0, s,
                                jobs, lambda, 0, 1, G);
         if (D.max_m > 0)
-            hipLaunchKernelGGL(lbp_clause_kernel, dim3(blocks(D.max_m), D.n_jobs), dim3(kLbpThreads), 0, s, jobs, w, 0,
+            hipLaunchKernelGGL(lbp_edge_kernel, dim3(blocks(4 * D.max_m), D.n_jobs), dim3(kLbpThreads), 0, s, jobs, w,
                                1, k & 1);
-    }
-    if (count > 0) {
-        const int last = first + count - 1;
-        hipLaunchKernelGGL(lbp_judge_kernel, dim3(1, D.n_jobs), dim3(1), 0, s, jobs,
-                           LbpJudge{last & 1, -1, last + 1, max_iter, tol});
     }
     return hipGetLastError();
 }
 
+// the batch's last iteration (`last`) judged; for the runs whose step has
+// stopped, the marginals and overlaps at this lambda and the outcome for the
+// host
+hipError_t lbp_launch_step_end(const LbpJob *jobs, const LbpDims &D, double lambda, double tol, int max_iter, int last,
+                               hipStream_t s) {
+    const LbpJudge G{last & 1, -1, last + 1, max_iter, tol};
+    if (D.max_n > 0)
+        hipLaunchKernelGGL(lbp_var_kernel, dim3(blocks(D.max_n * kVarLanes), D.n_jobs), dim3(kLbpThreads), 0, s, jobs,
+                           lambda, 1, 2, G);
+    hipLaunchKernelGGL(lbp_overlap_kernel, dim3(1, D.n_jobs), dim3(1024), 0, s, jobs, 1);
+    return hipGetLastError();
+}
+
 hipError_t lbp_launch_overlap(const LbpJob *jobs, const LbpDims &D, hipStream_t s) {
-    hipLaunchKernelGGL(lbp_overlap_kernel, dim3(1, D.n_jobs), dim3(1024), 0, s, jobs);
+    hipLaunchKernelGGL(lbp_overlap_kernel, dim3(1, D.n_jobs), dim3(1024), 0, s, jobs, 0);
     return hipGetLastError();
 }
 
