@@ -6,26 +6,16 @@
 // clause pins nothing.  White sets only grow and the pin condition only
 // weakens as they grow, so every inspection order that repeats until
 // nothing changes reaches the same (least) fixed point: the whitening of one
-// group of 4 replicas runs inside one workgroup, pass after pass, with no
-// global synchronization; the 16 chunks of a round are all read before any is
-// stored, so the number of passes does not depend on the waves' timing.
+// group of 4 replicas runs inside one workgroup, in place, pass after pass,
+// with no global synchronization.
 //
-// LDS: one byte per literal at the sweep's spin-table addresses (x_v at v, its
-// negation at N + v, always-false 2N, always-true 2N + 1): in the low nibble
-// whether the literal is true in each of the 4 replicas, in the high one the
-// variable's white bits, so the OR of a clause's other literals' bytes holds
-// both "another literal is true" and "another variable is white".  The
-// clause structure is the sweep's: per variable (a lane of a 64-variable
-// chunk), one 8-byte record per clause slot holding the addresses of the
-// clause's other literals and whether the variable's own literal is negated.
-// Padding slots (always-true first address) never pin.
-//
-// Bound: like a sweep, the three gathers per slot and the record stream.  With
-// one 16-bit word per variable, decoded by sign on every read, and records
-// loaded one slot at a time, the 12 passes over N = 50,000, 1024 replicas took
-// 12.5 ms; with this table and eight slots of records in flight they take 2.9
-// (2.7 without the rounds' barriers), 17 passes over N = 8422, 256 replicas 0.91
-// instead of 2.94.
+// LDS: one 16-bit word per variable, low byte the 4 replicas' spins, high
+// byte their white bits.  The clause structure is the sweep's: per variable
+// (a lane of a 64-variable chunk), one 8-byte record per clause slot holding
+// the spin-table addresses of the clause's other literals (x_v at v, its
+// negation at N + v, always-false 2N, always-true 2N + 1) and whether the
+// variable's own literal is negated.  Padding slots (always-true first
+// address) never pin.
 #include <climits>
 
 #include "nmc_internal.h"
@@ -34,98 +24,68 @@ namespace nmc {
 
 namespace {
 
+// spins and white bits of the literal at spin-table address a:
+// returns (truth bits) | (white bits << 8) of the other literal
+__device__ __forceinline__ uint32_t lit_state(const uint16_t *tbl, uint32_t a, uint32_t n, uint32_t amask) {
+    if (a < 2u * n) {
+        const uint32_t neg = a >= n ? 1u : 0u;
+        const uint32_t e = tbl[a - neg * n];
+        return ((e & 0xFFu) ^ (neg ? amask : 0u)) | (e & 0xFF00u);
+    }
+    return a == 2u * n + 1u ? amask : 0u;
+}
+
 __global__ void __launch_bounds__(1024) ksat_whiten_kernel(KsatDev I, const uint8_t *xs, int n_rep, uint8_t *white_out,
                                                            int32_t *frozen_out, int32_t *passes_out) {
-    extern __shared__ __align__(16) uint8_t tbl[];
+    extern __shared__ __align__(16) uint8_t smem[];
     __shared__ int changed;
     __shared__ int cnt[4];
+    uint16_t *tbl = reinterpret_cast<uint16_t *>(smem);
     const int n = I.n, g = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, nwaves = blockDim.x >> 6;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = threadIdx.x, lane = tid & 63, nwaves = blockDim.x >> 6, wave = tid >> 6;
     const int r0 = g * kGroup;
     const int nact = min(kGroup, n_rep - r0);
     const uint32_t amask = (1u << nact) - 1u;
     const uint8_t *xg = xs + (size_t)g * n;
-    for (int v = tid; v < n; v += blockDim.x) {
-        const uint32_t x = xg[v] & amask;
-        tbl[v] = (uint8_t)x;
-        tbl[n + v] = (uint8_t)(~x & amask);
-    }
-    if (tid == 0) {
-        tbl[2 * n] = 0;
-        tbl[2 * n + 1] = (uint8_t)amask;
-    }
+    for (int v = tid; v < n; v += blockDim.x)
+        tbl[v] = (uint16_t)(xg[v] & amask);
     if (tid < 4)
         cnt[tid] = 0;
-    const __amdgpu_buffer_rsrc_t recs =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t *>(I.rec), 0, (int)I.rec_bytes, kBufferWord3);
+    const uint64_t *rec = I.rec;
     int passes = 0;
     for (;;) {
         if (tid == 0)
             changed = 0;
         __syncthreads();
-        // rounds of one chunk per wave: every wave's reads, then its stores
-        for (int h0 = 0; h0 < I.n_chunks; h0 += nwaves) {
-            const int h = h0 + wave;
-            int i = 0, lg = 0;
-            uint32_t xi = 0, si = 0, ns = 0;
-            bool live = false;
-            if (h < I.n_chunks) {
-                const int lw = I.chunk_var[(size_t)h * kChunk + lane];
-                const int2 info = I.chunk_info[h];
-                const int nslot = __builtin_amdgcn_readfirstlane(info.y & ((1 << kSplitShift) - 1));
-                lg = __builtin_amdgcn_readfirstlane(info.y >> kSplitShift);  // 2^lg lanes per variable
-                i = lw & 0xFFFFF;
-                const uint32_t own = lw < 0 ? 0u : tbl[i];
-                xi = own & 0xFu;
-                si = own >> 4;
-                // the lanes of one variable agree on skipping it
-                live = lw >= 0 && si != amask;
-                if (__any(live)) {
-                    uint32_t pinned = 0;
-                    auto step = [&](uint32_t lo, uint32_t hi) {
-                        const uint32_t o = tbl[lo & kAddrMask] |
-                                           tbl[__builtin_amdgcn_alignbit(hi, lo, kAddrBits) & kAddrMask] |
-                                           tbl[__builtin_amdgcn_ubfe(hi, 2 * kAddrBits - 32, kAddrBits)];
-                        const uint32_t sm = (uint32_t)__builtin_amdgcn_sbfe(hi, 3 * kAddrBits - 32, 1);
-                        pinned |= (xi ^ sm) & ~(o | (o >> 4));
-                    };
-                    // 8 slots of records in flight (nslot is a multiple of 4;
-                    // past the last pair it is read again, which changes nothing)
-                    const int row0 = __builtin_amdgcn_readfirstlane(info.x) / 2, last = nslot / 2 - 1;
-                    auto rp = [&](int row) -> uint4 {
-                        return __builtin_bit_cast(
-                            uint4, __builtin_amdgcn_raw_buffer_load_b128(recs, lane * 16,
-                                                                         (row0 + min(row, last)) * (kChunk * 16), 0));
-                    };
-                    uint4 q[4] = {rp(0), rp(1), rp(2), rp(3)};
-                    for (int k = 0; k < nslot / 2; k += 4) {
-                        step(q[0].x, q[0].y);
-                        step(q[0].z, q[0].w);
-                        step(q[1].x, q[1].y);
-                        step(q[1].z, q[1].w);
-                        q[0] = rp(k + 4);
-                        q[1] = rp(k + 5);
-                        step(q[2].x, q[2].y);
-                        step(q[2].z, q[2].w);
-                        step(q[3].x, q[3].y);
-                        step(q[3].z, q[3].w);
-                        q[2] = rp(k + 6);
-                        q[3] = rp(k + 7);
-                    }
-                    pinned &= amask;
-                    for (int off = 1; off < (1 << lg); off <<= 1)
-                        pinned |= (uint32_t)__shfl_xor((int)pinned, off, 64);
-                    ns = si | (~pinned & amask);
-                }
+        for (int h = wave; h < I.n_chunks; h += nwaves) {
+            const int lw = I.chunk_var[(size_t)h * kChunk + lane];
+            const int2 info = I.chunk_info[h];
+            const int nslot = info.y & ((1 << kSplitShift) - 1);
+            const int lg = info.y >> kSplitShift;  // a variable's records spread over 2^lg lanes
+            const int i = lw & 0xFFFFF;
+            const uint32_t own = lw < 0 ? 0u : tbl[i];
+            const uint32_t xi = own & 0xFFu, si = own >> 8;
+            // the lanes of one variable agree on skipping it
+            const bool live = lw >= 0 && si != amask;
+            uint32_t pinned = 0;
+            for (int s = 0; live && s < nslot; ++s) {
+                const uint64_t r = rec[((size_t)(info.x / 2 + s / 2) * kChunk + lane) * 2 + (s & 1)];
+                const uint32_t a0 = (uint32_t)r & kAddrMask;
+                const uint32_t a1 = (uint32_t)(r >> kAddrBits) & kAddrMask;
+                const uint32_t a2 = (uint32_t)(r >> (2 * kAddrBits)) & kAddrMask;
+                const uint32_t neg = (uint32_t)(r >> (3 * kAddrBits)) & 1u;
+                const uint32_t own_true = neg ? (~xi & amask) : xi;
+                const uint32_t o = lit_state(tbl, a0, n, amask) | lit_state(tbl, a1, n, amask) |
+                                   lit_state(tbl, a2, n, amask);
+                pinned |= own_true & ~(o & 0xFFu) & ~(o >> 8);
             }
-            __syncthreads();
+            for (int off = 1; off < (1 << lg); off <<= 1)
+                pinned |= (uint32_t)__shfl_xor((int)pinned, off, 64);
+            const uint32_t ns = si | (~pinned & amask);
             if (live && (lane & ((1 << lg) - 1)) == 0 && ns != si) {
-                tbl[i] = (uint8_t)((ns << 4) | xi);
-                tbl[n + i] = (uint8_t)((ns << 4) | (~xi & amask));
+                tbl[i] = (uint16_t)((ns << 8) | xi);
                 changed = 1;
             }
-            __syncthreads();
         }
         __syncthreads();
         ++passes;
@@ -138,7 +98,7 @@ __global__ void __launch_bounds__(1024) ksat_whiten_kernel(KsatDev I, const uint
     int f0 = 0, f1 = 0, f2 = 0, f3 = 0;
     uint8_t *wg = white_out + (size_t)g * n;
     for (int v = tid; v < n; v += blockDim.x) {
-        const uint32_t w = tbl[v] >> 4;
+        const uint32_t w = tbl[v] >> 8;
         wg[v] = (uint8_t)w;
         const uint32_t fz = ~w & amask;
         f0 += fz & 1u;
@@ -167,7 +127,7 @@ __global__ void __launch_bounds__(1024) ksat_whiten_kernel(KsatDev I, const uint
 
 }  // namespace
 
-size_t ksat_whiten_lds_bytes(int n) { return align_up((size_t)n * 2 + 2, 16); }
+size_t ksat_whiten_lds_bytes(int n) { return align_up((size_t)n * 2, 16); }
 
 hipError_t ksat_launch_whiten(const KsatDev &I, const uint8_t *xs, int n_groups, int n_rep, uint8_t *white_out,
                               int32_t *frozen_out, int32_t *passes_out, hipStream_t s) {
