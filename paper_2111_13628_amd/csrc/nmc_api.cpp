@@ -191,6 +191,9 @@ struct nmc_instance {
     size_t off_sp_rec = 0, off_sp_var = 0, off_sp_info = 0, off_sp_color = 0;
     uint32_t sp_rec_bytes = 0;
     int32_t sp_lg = 0, sp_chunks = 0, sp_waves = 0;
+    // sweep layout (see KsatDev)
+    size_t off_bl_rec = 0, off_bl_var = 0, off_bl_info = 0, off_bl_color = 0;
+    uint32_t bl_rec_bytes = 0;
     // wide layout (spins in device memory; see nmc_ksat_wide.hip)
     bool wide = false;
     size_t off_wrec = 0, off_worder = 0, off_wclass = 0;
@@ -230,6 +233,11 @@ struct nmc_instance {
         d.sp_lg = sp_lg;
         d.sp_chunks = sp_chunks;
         d.sp_waves = sp_waves;
+        d.bl_rec = reinterpret_cast<const uint32_t *>(dev + off_bl_rec);
+        d.bl_var = reinterpret_cast<const int32_t *>(dev + off_bl_var);
+        d.bl_info = reinterpret_cast<const int4 *>(dev + off_bl_info);
+        d.bl_color = reinterpret_cast<const int32_t *>(dev + off_bl_color);
+        d.bl_rec_bytes = bl_rec_bytes;
         d.wrec = reinterpret_cast<const uint4 *>(dev + off_wrec);
         d.worder = reinterpret_cast<const int32_t *>(dev + off_worder);
         d.wclass_ptr = reinterpret_cast<const int32_t *>(dev + off_wclass);
@@ -302,6 +310,16 @@ uint64_t pack_rec(const ChunkRec &r) {
            ((uint64_t)r.neg << (3 * kAddrBits));
 }
 
+// The 8-byte record of the sweep layout: every word's low 17 bits hold an
+// address, the two high bytes bits 0..15 of the third, whose bit 16 is the first
+// one's (of three addresses two agree in it; the order has no meaning).
+uint64_t pack_rec_pair(ChunkRec r) {
+    if ((r.a[0] ^ r.a[2]) >> 16)
+        std::swap(r.a[1], (r.a[0] ^ r.a[1]) >> 16 ? r.a[0] : r.a[2]);
+    const uint32_t lo = r.a[0] | (r.a[2] & 0xFFu) << 24, hi = r.a[1] | (r.a[2] >> 8 & 0xFFu) << 24;
+    return (uint64_t)lo | (uint64_t)hi << 32;
+}
+
 // Bank model of one byte gather on gfx950 LDS: 32 banks of 4 bytes, a wave's
 // 64 addresses served in two half-waves of 32; lanes reading the same dword
 // share one access, different dwords on one bank serialize.  Cost of a
@@ -339,9 +357,10 @@ struct BankLoad {
 // bank in each half-wave.  Greedy per slot: lanes take, in turn, the record
 // and address order that raises the half-wave's worst bank least, then loads
 // the fewest-used banks; the most loaded lanes go first.  Any placement gives
-// the same results; only the gathers' bank conflicts change.
+// the same results; only the gathers' bank conflicts change.  With pair16 the
+// first and third addresses of a record agree in bit 16 (see pack_rec_pair).
 void schedule_chunk(std::vector<std::vector<ChunkRec>> &lanes, int32_t nslot, bool optimize,
-                    std::vector<ChunkRec> &out /* [nslot][64] */, const ChunkRec &dummy) {
+                    std::vector<ChunkRec> &out /* [nslot][64] */, const ChunkRec &dummy, bool pair16 = false) {
     static const int perms[6][3] = {{0, 1, 2}, {1, 2, 0}, {2, 0, 1}, {0, 2, 1}, {1, 0, 2}, {2, 1, 0}};
     out.assign((size_t)nslot * kChunk, dummy);
     if (!optimize) {
@@ -374,6 +393,8 @@ void schedule_chunk(std::vector<std::vector<ChunkRec>> &lanes, int32_t nslot, bo
             int best_i = 0, best_p = 0, best_c = 1 << 30;
             for (size_t i = 0; i < rem.size() && best_c > 0; ++i)
                 for (int p = 0; p < 6 && best_c > 0; ++p) {
+                    if (pair16 && (rem[i].a[perms[p][0]] ^ rem[i].a[perms[p][2]]) >> 16)
+                        continue;
                     int c = 0;
                     for (int j = 0; j < 3; ++j) {
                         const int a = load[j][h].after((int32_t)(rem[i].a[perms[p][j]] >> 2));
@@ -711,6 +732,148 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
             I->sp_lg = lg;
             I->sp_chunks = (int32_t)sp_info.size();
         }
+        // sweep layout: chunks of one class with lengths as equal as possible,
+        // since a class ends when its longest wave does.  A class of K chunks
+        // runs in rounds of kLayoutWaves; if the last round would hold half of
+        // them or fewer, its variables (those of middle degree) take 2^lg lanes
+        // each.  (With a single round that would multiply the decisions of the
+        // batched sweeps, which run such classes on fewer waves: there only a
+        // last chunk of few variables is spread, over its own lanes.)  All others go in pairs of a heavy variable (even lane) and a
+        // light one (odd lane): the light lane walks `ws` slots of its own, then
+        // the heavy one's remaining clauses.
+        std::vector<uint32_t> bl_rec;
+        std::vector<int32_t> bl_var, bl_color(ncol + 1, 0);
+        std::vector<int4> bl_info;
+        if (!I->wide) {
+            // a chunk is placed in two parts: slots below ws, slots from ws on
+            struct SweepChunk {
+                std::vector<std::vector<ChunkRec>> lanes[2];
+                std::vector<ChunkRec> placed[2];
+            };
+            std::vector<SweepChunk> work;
+            int32_t bytes = 0;  // (below 2^31: N <= 65534 and degree <= 127)
+            auto deg = [&](int32_t v) { return vptr[v + 1] - vptr[v]; };
+            auto even = [](int32_t x) { return (x + 1) / 2 * 2; };
+            auto rec_of = [&](int32_t q) {
+                const int32_t a = vcl[q], own = vpos[q];
+                ChunkRec r{{ZERO, ZERO, ZERO}, lits[own] < 0 ? 1u : 0u};
+                int k = 0;
+                for (int32_t p = clause_ptr[a]; p < clause_ptr[a + 1]; ++p)
+                    if (p != own)
+                        r.a[k++] = lit_addr(lits[p]);
+                return r;
+            };
+            // lane word of variable v with `slots` slots (padding among them)
+            auto lane_word = [&](int32_t v, int32_t slots) {
+                int32_t neg = 0;
+                for (int32_t q = vptr[v]; q < vptr[v + 1]; ++q)
+                    neg += lits[vpos[q]] < 0;
+                return v | (int32_t)((uint32_t)(slots - neg) << 20);
+            };
+            auto add_chunk = [&](SweepChunk &&w, int32_t nslot, int32_t lg, int32_t ws) {
+                bl_info.push_back(make_int4(bytes, nslot, lg, ws));
+                bytes += (nslot + 7) / 8 * kBlockSign + nslot / 2 * kBlockRow;
+                work.push_back(std::move(w));
+            };
+            for (int32_t c = 0; c < ncol; ++c) {
+                std::vector<int32_t> vs(I->order.begin() + I->color_ptr[c], I->order.begin() + I->color_ptr[c + 1]);
+                std::stable_sort(vs.begin(), vs.end(), [&](int32_t x, int32_t y) { return deg(x) > deg(y); });
+                const int32_t V = (int32_t)vs.size(), K = (V + kChunk - 1) / kChunk, rem = K % kLayoutWaves;
+                int32_t lg = 0, nv = 0;  // variables on 2^lg lanes: vs[first, first + nv)
+                if (K > kLayoutWaves) {
+                    while (split && rem > 0 && lg < kMaxSplitLog && rem << (lg + 1) <= kLayoutWaves)
+                        ++lg;
+                    nv = lg ? V - (K - rem) * kChunk : 0;
+                } else {
+                    while (split && lg < kMaxSplitLog && V % kChunk << (lg + 1) <= kChunk)
+                        ++lg;
+                    nv = lg ? V % kChunk : 0;
+                }
+                const int32_t first = (V - nv) / 2;
+                const int32_t L = 1 << lg, per = kChunk >> lg;
+                std::vector<int32_t> ps(vs.begin(), vs.begin() + first);
+                ps.insert(ps.end(), vs.begin() + first + nv, vs.end());
+                const int32_t P = (int32_t)ps.size(), pairs = (P + 1) / 2;
+                for (int32_t b = 0; b < pairs; b += kChunk / 2) {
+                    const int32_t e = std::min(pairs, b + kChunk / 2);
+                    int32_t ws = 2, nslot = 2;
+                    for (int32_t i = b; i < e; ++i)
+                        if (P - 1 - i > i)
+                            ws = std::max(ws, even(deg(ps[P - 1 - i])));
+                    for (int32_t i = b; i < e; ++i)
+                        nslot = std::max(nslot, std::max(ws, even((deg(ps[i]) + ws + 1) / 2)));
+                    SweepChunk w;
+                    w.lanes[0].resize(kChunk);
+                    w.lanes[1].resize(kChunk);
+                    std::vector<int32_t> lw(kChunk, -1);
+                    for (int32_t i = b; i < e; ++i) {
+                        const int32_t l = 2 * (i - b), hv = ps[i], d = deg(hv);
+                        for (int32_t k = 0; k < d; ++k)
+                            (k < ws ? w.lanes[0][l] : k < nslot ? w.lanes[1][l] : w.lanes[1][l + 1])
+                                .push_back(rec_of(vptr[hv] + k));
+                        lw[l] = lane_word(hv, 2 * nslot - ws);
+                        if (P - 1 - i > i) {
+                            const int32_t v = ps[P - 1 - i];
+                            for (int32_t q = vptr[v]; q < vptr[v + 1]; ++q)
+                                w.lanes[0][l + 1].push_back(rec_of(q));
+                            lw[l + 1] = lane_word(v, ws);
+                        }
+                    }
+                    bl_var.insert(bl_var.end(), lw.begin(), lw.end());
+                    add_chunk(std::move(w), nslot, 0, ws);
+                }
+                for (int32_t b = first; b < first + nv; b += per) {
+                    const int32_t e = std::min(first + nv, b + per);
+                    // (descending degrees: the first variable has the most clauses)
+                    const int32_t nslot = std::max(2, even((deg(vs[b]) + L - 1) / L));
+                    SweepChunk w;
+                    w.lanes[0].resize(kChunk);
+                    w.lanes[1].resize(kChunk);
+                    std::vector<int32_t> lw(kChunk, -1);
+                    for (int32_t i = b; i < e; ++i) {
+                        const int32_t l = (i - b) * L;
+                        for (int32_t k = 0; k < deg(vs[i]); ++k)
+                            w.lanes[0][l + k % L].push_back(rec_of(vptr[vs[i]] + k));
+                        lw[l] = lane_word(vs[i], L * nslot);
+                    }
+                    bl_var.insert(bl_var.end(), lw.begin(), lw.end());
+                    add_chunk(std::move(w), nslot, lg, nslot);
+                }
+                bl_color[c + 1] = (int32_t)bl_info.size();
+            }
+            const ChunkRec dummy{{ONES, ZERO, ZERO}, 0u};
+            std::atomic<size_t> next{0};
+            bl_rec.resize((size_t)bytes / 4);
+            auto worker = [&] {
+                for (size_t i; (i = next.fetch_add(1)) < work.size();) {
+                    const int4 f = bl_info[i];
+                    const int32_t nslot = f.y, ws = f.w;
+                    schedule_chunk(work[i].lanes[0], ws, bank_schedule, work[i].placed[0], dummy, true);
+                    schedule_chunk(work[i].lanes[1], nslot - ws, bank_schedule, work[i].placed[1], dummy, true);
+                    for (int32_t sl = 0; sl < nslot; ++sl) {
+                        uint32_t *block = bl_rec.data() + (size_t)(f.x + sl / 8 * kBlockBytes) / 4;
+                        const int last = std::min(nslot, (sl / 8 + 1) * 8) - 1;
+                        for (int lane = 0; lane < kChunk; ++lane) {
+                            const ChunkRec &r = sl < ws ? work[i].placed[0][(size_t)sl * kChunk + lane]
+                                                        : work[i].placed[1][(size_t)(sl - ws) * kChunk + lane];
+                            if (r.neg)
+                                block[lane] |= 0xFu << (4 * (last - sl));
+                            const uint64_t w = pack_rec_pair(r);
+                            std::memcpy(block + (kBlockSign + sl % 8 / 2 * kBlockRow) / 4 + lane * 4 + sl % 2 * 2, &w, 8);
+                        }
+                    }
+                    work[i] = SweepChunk();
+                }
+            };
+            const unsigned nt =
+                bank_schedule && vcl.size() >= 20000 ? std::min(8u, std::max(1u, std::thread::hardware_concurrency())) : 1u;
+            std::vector<std::thread> pool;
+            for (unsigned t = 1; t < nt; ++t)
+                pool.emplace_back(worker);
+            worker();
+            for (auto &t : pool)
+                t.join();
+        }
         // wide layout: per incidence (var_ptr order) the clause's other
         // literals as spin-table rows (v for x_v, n + 1 + v for NOT x_v, row
         // n: absent, never true), and whether the variable's own literal is
@@ -783,6 +946,13 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
             I->off_sp_info = ar.take(sp_info.size() * 8);
             I->off_sp_color = ar.take(sp_color.size() * 4);
         }
+        if (!I->wide) {
+            I->off_bl_rec = ar.take(bl_rec.size() * 4);
+            I->bl_rec_bytes = (uint32_t)(bl_rec.size() * 4);
+            I->off_bl_var = ar.take(bl_var.size() * 4);
+            I->off_bl_info = ar.take(bl_info.size() * 16);
+            I->off_bl_color = ar.take(bl_color.size() * 4);
+        }
         if (I->wide) {
             I->off_wrec = ar.take(std::max<size_t>(wrec.size() * sizeof(uint4), 16));
             I->off_worder = ar.take((size_t)n * 4);
@@ -810,6 +980,12 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
             put(I->off_sp_var, sp_var.data(), sp_var.size() * 8);
             put(I->off_sp_info, sp_info.data(), sp_info.size() * 8);
             put(I->off_sp_color, sp_color.data(), sp_color.size() * 4);
+        }
+        if (!I->wide) {
+            put(I->off_bl_rec, bl_rec.data(), bl_rec.size() * 4);
+            put(I->off_bl_var, bl_var.data(), bl_var.size() * 4);
+            put(I->off_bl_info, bl_info.data(), bl_info.size() * 16);
+            put(I->off_bl_color, bl_color.data(), bl_color.size() * 4);
         }
         if (I->wide) {
             put(I->off_wrec, wrec.data(), wrec.size() * sizeof(uint4));

@@ -46,6 +46,9 @@ constexpr int kSlotUnroll = 4;  // clause slots per chunk are padded to a multip
 // first of which (lane % 2^lg == 0) takes the decision.
 constexpr int kSplitShift = 16;
 constexpr int kMaxSplitLog = 4;
+// The sweep layout balances a colour class over this many waves.
+constexpr int kLayoutWaves = 16;
+constexpr int kBlockSign = kChunk * 4, kBlockRow = kChunk * 16, kBlockBytes = kBlockSign + 4 * kBlockRow;
 
 // The split layout: instances of at most kSplitMaxVars variables whose colour
 // classes hold kSplitMaxClass variables or fewer on average.
@@ -59,6 +62,7 @@ __host__ __device__ inline size_t align_up(size_t v, size_t a) { return (v + a -
 
 // Device view of a bound k-SAT instance.
 struct KsatDev {
+    // chunks of the whitening passes (the sweeps have a layout of their own)
     const uint64_t *rec;         // chunk records, [slot-row][64 lanes]
     const int32_t *chunk_var;    // [n_chunks][64] lane word: variable | negated-count << 20, -1 = empty
     const int2 *chunk_info;      // [n_chunks] (first slot-row, slot count | lg << kSplitShift)
@@ -69,7 +73,7 @@ struct KsatDev {
     const uint32_t *lbp_caddr;   // [M][4] clause_addr in the LBP clause order (clauses by smallest variable)
     const int32_t *lbp_pos;      // [M] position of each clause in the LBP clause order
     int32_t n, m, n_colors, n_chunks, dmax;
-    uint32_t rec_bytes;          // size of rec in bytes (the bound of the sweep's buffer loads)
+    uint32_t rec_bytes;          // size of rec in bytes (the bound of buffer loads)
     // split layout (small colour classes; sp_lg = 0: none): each variable on
     // 2^sp_lg lanes in every chunk, records in 16-byte pairs of slots
     const uint64_t *sp_rec;      // [pair-row][64 lanes][2]
@@ -79,6 +83,15 @@ struct KsatDev {
     const int32_t *sp_color;     // [n_colors + 1] chunk range of each colour class
     uint32_t sp_rec_bytes;
     int32_t sp_lg, sp_chunks, sp_waves;  // sp_waves: most chunks of a class, at most 16
+    // sweep layout (instances that are not wide): a chunk is a sequence of
+    // blocks of 8 slots: the signs of a lane's 8 slots (a nibble each, the last
+    // slot's lowest: 0xF where the own literal is negated), then the records in
+    // pairs, 16 bytes a lane; the last block holds 2, 4, 6 or 8 slots
+    const uint32_t *bl_rec;      // [block]([64 lanes], [pair][64 lanes][2 records of 8 bytes])
+    const int32_t *bl_var;       // [chunk][64] variable | share of the closed form << 20, -1: decides nothing
+    const int4 *bl_info;         // [chunk] (byte offset in bl_rec, slots, lg, slots of an odd lane's own variable)
+    const int32_t *bl_color;     // [n_colors + 1] chunk range of each colour class
+    uint32_t bl_rec_bytes;
     // wide layout (wide != 0; rec and the chunk arrays are then empty)
     const uint4 *wrec;           // [sum deg] per incidence in var_ptr order: the clause's other three
                                  // literals as row | negated << 31 (row N: absent, never true), own sign

@@ -16,7 +16,7 @@
 // computed for the 4 replicas at once: the OR of the other literals' bytes
 // is a 4-bit "satisfied by others" mask, spread into four byte lanes of a
 // 32-bit accumulator (SIMD within a register).
-// A wave handles 64 variables of one colour class (one lane per variable);
+// A wave handles up to 64 variables of one colour class;
 // classes are conflict-free, so all lanes update concurrently and the result
 // equals the sequential colour-major order.  The instance (per-variable
 // clause records) streams from L2/MALL, shared by every workgroup.
@@ -68,6 +68,7 @@ __device__ __forceinline__ void issue_fence() { __asm__ volatile("" ::: "memory"
 
 typedef __attribute__((address_space(3))) const uint8_t lds_cu8;
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 // Byte at LDS address a.  The sweep kernel declares no static LDS, so its
 // dynamic LDS block starts at address 0 and spin-table offsets are addresses.
@@ -162,17 +163,41 @@ __global__ void ksat_reset_tallies_kernel(KsatRepDev R) {
     }
 }
 
-// One clause slot for the 8 replicas of two groups (spin bytes holding the
-// first group in bits 0..3, the second in bits 4..7): the same record and
-// gathers feed both accumulators.
-__device__ __forceinline__ void slot_step2(uint32_t &a0, uint32_t &a1, uint2 r) {
-    const uint32_t ad0 = r.x & kAddrMask;
-    const uint32_t ad1 = __builtin_amdgcn_alignbit(r.y, r.x, kAddrBits) & kAddrMask;
-    const uint32_t ad2 = __builtin_amdgcn_ubfe(r.y, 2 * kAddrBits - 32, kAddrBits);
-    const uint32_t sm = (uint32_t)__builtin_amdgcn_sbfe(r.y, 3 * kAddrBits - 32, 1);
-    const uint32_t sat = lds_load_u8(ad0) | lds_load_u8(ad1) | lds_load_u8(ad2);
-    a0 = (spread4(sat & 0xFu) ^ sm) + a0;
-    a1 = (spread4(sat >> 4) ^ sm) + a1;
+// Arrays that no kernel writes, read at wave-uniform indexes into scalar
+// registers.
+template <class T>
+__device__ __forceinline__ T scalar_read(const T *p, int i) {
+    typedef const T __attribute__((address_space(4))) *cp;
+    return ((cp)(uintptr_t)p)[i];
+}
+
+// The three gathered bytes of a sweep-layout record, and their union (as 32-bit
+// words: the compiler is kept from forming it in 16 bits and extending it).
+struct SlotBytes {
+    uint32_t x[3];
+};
+struct SlotPair {
+    SlotBytes a, b;
+};
+__device__ __forceinline__ SlotBytes slot_bytes(uint32_t lo, uint32_t hi) {
+    // the third address: the words' high bytes, and bit 16 (byte 2) of the first
+    return {{lds_load_u8(lo & kAddrMask), lds_load_u8(hi & kAddrMask),
+             lds_load_u8(__builtin_amdgcn_perm(hi, lo, 0x0C020703u))}};
+}
+__device__ __forceinline__ uint32_t slot_sat(SlotBytes b) {
+    __asm__("" : "+v"(b.x[0]), "+v"(b.x[1]), "+v"(b.x[2]));
+    return b.x[0] | b.x[1] | b.x[2];
+}
+
+// cnt[j] += set bits of the nibbles of w at replica j.
+__device__ __forceinline__ void count_nibbles(uint32_t (&cnt)[4], uint32_t w) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        cnt[j] += (uint32_t)__builtin_popcount(w & (0x11111111u << j));
+}
+
+__device__ __forceinline__ uint32_t pack_counts(const uint32_t (&c)[4]) {
+    return c[0] + (c[1] << 8) + (c[2] << 16) + (c[3] << 24);
 }
 
 // n_sweeps full sweeps of every colour class for the replicas of item g, by
@@ -181,6 +206,20 @@ __device__ __forceinline__ void slot_step2(uint32_t &a0, uint32_t &a1, uint2 r) 
 // and 2g + 1, held in one spin byte per variable (first group in bits 0..3),
 // so every clause record, address decode and LDS gather serves 8 replicas;
 // the random words and every result are those of the groups run one by one.
+//
+// Bound: a class step (one chunk per wave, then a barrier) takes the LDS
+// gathers of all waves (3.8 cycles each, two thirds of the time) and one
+// decision.  The sweep layout serves both: chunks of a class have one length (a
+// heavy variable's last clauses are walked by its light neighbour's lane;
+// lengths of 28 to 60 slots at degree 40 left early waves waiting), a slot takes
+// 6 vector instructions instead of 9 (signs are words of their own, satisfied
+// slots are collected as nibbles and counted 8 at a time, an address takes one
+// instruction), chunk descriptors are read as scalars one chunk ahead and the
+// first records before the class barrier.  N = 50,000, 1024 replicas: 285 -> 257
+// us per sweep; 4096 replicas of N = 20,000: 577 -> 490; 3-SAT N = 30,000, 512
+// replicas: 86 -> 71.  Tried: the generator's rounds spread over the slot loop
+// (263, small instances slower), one loop for whole and short blocks (copies of
+// the records in flight, 278), rows past a short block left out (263).
 template <int GPW>
 __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &R, const SweepCall &C, const int g,
                                             uint8_t *smem) {
@@ -255,7 +294,65 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
     uint32_t n_acc = 0;  // flips this lane accepted in this call
     // the instance's records (out-of-range offsets would read zeros)
     const __amdgpu_buffer_rsrc_t recs =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t *>(I.rec), 0, (int)I.rec_bytes, kBufferWord3);
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(I.bl_rec), 0, (int)I.bl_rec_bytes, kBufferWord3);
+    auto sign_at = [&](int at) { return __builtin_amdgcn_raw_buffer_load_b32(recs, lane * 4, at, 0); };
+    auto row_at = [&](int at, int row) -> uint4 {
+        return __builtin_bit_cast(
+            uint4, __builtin_amdgcn_raw_buffer_load_b128(recs, lane * 16, at + kBlockSign + row * kBlockRow, 0));
+    };
+    // the four waves of a SIMD at four priorities: chunks of one length would
+    // otherwise all gather, then all decide (264 -> 257 us per sweep)
+    switch (wave_u >> 2 & 3) {
+    case 0: __builtin_amdgcn_s_setprio(3); break;
+    case 1: __builtin_amdgcn_s_setprio(2); break;
+    case 2: __builtin_amdgcn_s_setprio(1); break;
+    default: __builtin_amdgcn_s_setprio(0);
+    }
+    // A wave takes every nwaves-th chunk of a class.  While it works on one, the
+    // next one's descriptor is known (class next_c, chunk next_h), so that its
+    // first block can be read in time; after a sweep's last chunk (next_c =
+    // n_colors) that is the first one again.
+    int next_c = 0, next_h = wave_u, end_h = scalar_read(I.bl_color, 1);
+    auto skip = [&] {  // to the first chunk at or after next_h
+        while (next_h >= end_h && ++next_c < I.n_colors) {
+            next_h = end_h + wave_u;
+            end_h = scalar_read(I.bl_color, next_c + 1);
+        }
+    };
+    skip();
+    const int first_c = next_c, first_h = next_h, first_end = end_h;
+    const i32x4 *infos = reinterpret_cast<const i32x4 *>(I.bl_info);
+    i32x4 info = {0, 0, 0, 0}, next = {0, 0, 0, 0};
+    int lane_word = -1, chunk_c = first_c;  // the chunk at hand
+    uint32_t sign = 0;
+    uint4 q[4];
+    auto advance = [&] {
+        if (next_c == I.n_colors) {
+            next_c = first_c;
+            next_h = first_h;
+            end_h = first_end;
+        }
+        next_h += nwaves;
+        skip();
+        if (next_c == I.n_colors)
+            next_h = first_h;
+        next = scalar_read(infos, next_h);
+    };
+    // a block, with what follows one shorter than 8 slots (zeros past the end:
+    // out of the buffer's bounds); not used
+    auto read_block = [&](int at) {
+        sign = (uint32_t)sign_at(at);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            q[i] = row_at(at, i);
+    };
+    auto lane_words = [&](int h) { return I.bl_var[(size_t)h * kChunk + lane]; };
+    if (first_c < I.n_colors) {
+        info = scalar_read(infos, first_h);
+        lane_word = lane_words(first_h);
+        read_block(info.x);
+        advance();
+    }
     for (int s = 0; s < C.n_sweeps; ++s) {
         const uint32_t t = C.t0 + (uint32_t)s;
         const uint32_t *tg = tab + (size_t)s * C.sweep_words;
@@ -267,123 +364,149 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
 #pragma unroll
         for (int j = 0; j < NR; ++j)
             dsum[j] = 0;
-        for (int c = 0; c < I.n_colors; ++c) {
-            const int h0 = I.color_chunk[c], h1 = I.color_chunk[c + 1];
-            // chunks of a class are sorted by slot count (descending); rounds
-            // alternate direction so heavy and light chunks pair up per wave
-            const int nch = h1 - h0;
-            for (int rnd = 0; rnd * nwaves < nch; ++rnd) {
-                const int idx = rnd * nwaves + ((rnd & 1) ? nwaves - 1 - wave_u : wave_u);
-                if (idx >= nch)
-                    continue;
-                const int h = h0 + idx;
-                // after the class barrier every wave would start its gathers
-                // at once; delaying waves by (index mod 4) x 128 cycles spreads
-                // the workgroup's gathers on the shared LDS over time (measured
-                // 2 % faster on N = 50,000, 1024 replicas)
-                if (wave_u & 2)
-                    __builtin_amdgcn_s_sleep(4);
-                if (wave_u & 1)
-                    __builtin_amdgcn_s_sleep(2);
-                const int2 info = I.chunk_info[h];
-                const int nslot = __builtin_amdgcn_readfirstlane(info.y & ((1 << kSplitShift) - 1));
-                const int lg = __builtin_amdgcn_readfirstlane(info.y >> kSplitShift);
-                const int lw = I.chunk_var[(size_t)h * kChunk + lane];
-                // with lg > 0 a variable's clauses are spread over 2^lg lanes;
-                // the first of them takes the decision
-                const int v = (lw < 0 || (lane & ((1 << lg) - 1))) ? -1 : (lw & 0xFFFFF);
+        for (int cur = 0;;) {
+            // (a wave joins the barriers of the classes it has no chunk in)
+            for (; cur < chunk_c; ++cur)
+                __syncthreads();
+            if (chunk_c == I.n_colors)
+                break;
+            {
+                const int nslot = info.y, lg = info.z, ws = info.w, lw = lane_word;
+                const int v = lw < 0 ? -1 : (lw & 0xFFFFF);
                 // the variable's class is needed after the slot loop; load it now
                 const int cl = (C.var_cls && v >= 0) ? (int)C.var_cls[v] : 0;
-                // record row `row` of the chunk (16 bytes a lane) as a buffer
-                // load: the row's byte offset is a scalar operand and the
-                // lane's offset the same register for every row, so no vector
-                // instruction computes a record address
-                const int row0 = __builtin_amdgcn_readfirstlane(info.x) / 2;
-                auto rp = [&](int row) -> uint4 {
-                    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                         recs, lane * 16, (row0 + row) * (kChunk * 16), 0));
+                // 8 slots at a time: a word of nibbles (two words for two
+                // groups), one per slot, whose xor with the signs has a bit set
+                // where the slot's own literal is positive and another is true,
+                // or negated and none is; cnt adds those bits up per replica,
+                // cnf those of the slots from ws on, which in an odd lane are its
+                // neighbour's.  The next block's records are in flight.
+                uint32_t cnt[GPW][4] = {}, cnf[GPW][4] = {};
+                uint32_t word[GPW];
+                auto pair = [&](const uint4 &q) {
+                    const SlotBytes b0 = slot_bytes(q.x, q.y), b1 = slot_bytes(q.z, q.w);
+                    return SlotPair{b0, b1};
                 };
-                // acc collects sum over slots of (spread(sat) xor signmask); the
-                // closed form below turns it into 128 + dE-part per byte lane.
-                // Slots come in 16-byte pairs; 8 slots of records are in flight
-                // while 4 are consumed (nslot is a multiple of 4, at least 4; the
-                // pair index is clamped so every load is in bounds).
+                auto add = [&](const SlotPair &p) {
+                    const uint32_t x0 = slot_sat(p.a), x1 = slot_sat(p.b);
+                    if constexpr (GPW == 1) {
+                        word[0] = (word[0] << 4) | x0;
+                        word[0] = (word[0] << 4) | x1;
+                    } else {
+                        word[0] = (((word[0] << 4) | (x0 & 0xFu)) << 4) | (x1 & 0xFu);
+                        word[GPW - 1] = (((word[GPW - 1] << 4) | (x0 >> 4)) << 4) | (x1 >> 4);
+                    }
+                };
+                // the block's slots past ws are its low f nibbles
+                auto count = [&](uint32_t sg, int f) {
+#pragma unroll
+                    for (int k = 0; k < GPW; ++k)
+                        count_nibbles(cnt[k], word[k] ^ sg);
+                    if (f > 0) {
+                        const uint32_t m = f >= 8 ? ~0u : (1u << (4 * f)) - 1u;
+#pragma unroll
+                        for (int k = 0; k < GPW; ++k)
+                            count_nibbles(cnf[k], (word[k] ^ sg) & m);
+                    }
+                };
+                auto clear = [&] {
+#pragma unroll
+                    for (int k = 0; k < GPW; ++k)
+                        word[k] = 0;
+                };
+                int left = nslot, at = info.x;
+                for (; left > 8; left -= 8) {
+                    at += kBlockBytes;
+                    const uint32_t sg = sign;
+                    clear();
+                    const SlotPair p0 = pair(q[0]), p1 = pair(q[1]);
+                    sign = (uint32_t)sign_at(at);
+                    q[0] = row_at(at, 0);
+                    q[1] = row_at(at, 1);
+                    issue_fence();
+                    add(p0);
+                    add(p1);
+                    const SlotPair p2 = pair(q[2]), p3 = pair(q[3]);
+                    q[2] = row_at(at, 2);
+                    q[3] = row_at(at, 3);
+                    issue_fence();
+                    add(p2);
+                    add(p3);
+                    count(sg, nslot - left + 8 - ws);
+                }
+                // the last block
+                clear();
+                auto tail = [&](auto np) {
+                    constexpr int NP = decltype(np)::value;
+                    SlotPair p[NP];
+#pragma unroll
+                    for (int i = 0; i < NP; ++i)
+                        p[i] = pair(q[i]);
+                    issue_fence();
+#pragma unroll
+                    for (int i = 0; i < NP; ++i)
+                        add(p[i]);
+                };
+                switch (left) {
+                case 2: tail(std::integral_constant<int, 1>{}); break;
+                case 4: tail(std::integral_constant<int, 2>{}); break;
+                case 6: tail(std::integral_constant<int, 3>{}); break;
+                default: tail(std::integral_constant<int, 4>{});
+                }
+                count(sign, nslot - ws);
+                // on to the next chunk, while this one is decided
+                info = next;
+                read_block(info.x);
+                lane_word = lane_words(next_h);
+                chunk_c = next_c;
+                advance();
+                issue_fence();
+                // the closed form: (slots that are not negated) - count per
+                // replica, as four byte lanes around 128; sums and differences
+                // mod 2^32, so the lanes' shares add up in any order
                 uint32_t acc[GPW];
 #pragma unroll
-                for (int k = 0; k < GPW; ++k)
-                    acc[k] = 0;
-                auto step = [&](uint32_t x, uint32_t y) {
-                    if constexpr (GPW == 1)
-                        acc[0] = slot_step(acc[0], make_uint2(x, y));
-                    else
-                        slot_step2(acc[0], acc[GPW - 1], make_uint2(x, y));
-                };
-                const int lastp = nslot / 2 - 1;
-                uint4 q0 = rp(0), q1 = rp(min(1, lastp));
-                uint4 q2 = rp(min(2, lastp)), q3 = rp(min(3, lastp));
-                issue_fence();
-                // whole groups of 8 slots with one exit, then a tail of 4
-                int k = 0;
-                for (; k + 2 * kSlotUnroll <= nslot; k += 2 * kSlotUnroll) {
-                    step(q0.x, q0.y);
-                    step(q0.z, q0.w);
-                    step(q1.x, q1.y);
-                    step(q1.z, q1.w);
-                    q0 = rp(min(k / 2 + 4, lastp));
-                    q1 = rp(min(k / 2 + 5, lastp));
-                    issue_fence();
-                    step(q2.x, q2.y);
-                    step(q2.z, q2.w);
-                    step(q3.x, q3.y);
-                    step(q3.z, q3.w);
-                    q2 = rp(min(k / 2 + 6, lastp));
-                    q3 = rp(min(k / 2 + 7, lastp));
-                    issue_fence();
-                }
-                if (k < nslot) {
-                    step(q0.x, q0.y);
-                    step(q0.z, q0.w);
-                    step(q1.x, q1.y);
-                    step(q1.z, q1.w);
-                }
-                const uint32_t nneg = lw < 0 ? 0u : ((uint32_t)lw >> 20) & 0xFFu;
-                // the lane's share of the closed form (sums mod 2^32 add up
-                // across lanes: an inert padding slot contributes 0)
-#pragma unroll
                 for (int k = 0; k < GPW; ++k) {
-                    uint32_t part = ((uint32_t)nslot - 2u * nneg) * 0x01010101u - nneg - acc[k];
-                    for (int off = 1; off < (1 << lg); off <<= 1)
-                        part += (uint32_t)__shfl_xor((int)part, off, 64);
-                    acc[k] = 0x80808080u + part;
+                    uint32_t part = pack_counts(cnt[k]);
+                    if (lg > 0)
+                        part = lane_group_sum(part, lg);
+                    else if (ws < nslot) {
+                        // the odd lane's foreign slots: to the even lane
+                        const uint32_t own = pack_counts(cnf[k]);
+                        const uint32_t odd = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0xF5, 0xF, 0xF, false);
+                        part += (lane & 1) ? 0u - odd : odd;
+                    }
+                    // (the lane word's share in every byte)
+                    acc[k] = 0x80808080u + __builtin_amdgcn_perm(0u, (uint32_t)lw >> 20, 0u) - part;
                 }
                 if (v >= 0) {
                     const uint32_t xi = lds_load_u8((uint32_t)v);
-                    const uint32_t *T = tl + cl * C.stride;
+                    const uint32_t *T = tl + __mul24(cl, C.stride);
                     int de[NR];
-                    uint32_t thr[NR];
-                    uint32_t flip = 0, need = 0;
-#pragma unroll
-                    for (int j = 0; j < NR; ++j) {
-                        const int S = (int)((acc[j >> 2] >> (8 * (j & 3))) & 0xFFu) - 128;
-                        de[j] = ((xi >> j) & 1u) ? S : -S;
-                        thr[j] = T[max(de[j], 0)];
-                        const uint32_t on = (amask >> j) & 1u;
-                        flip |= (on & (uint32_t)(de[j] <= 0)) << j;
-                        need |= (on & (uint32_t)(de[j] > 0) & (uint32_t)(thr[j] != 0)) << j;
-                    }
+                    uint32_t flip = 0;
 #pragma unroll
                     for (int k = 0; k < GPW; ++k) {
-                        // one generator call per group gives its 4 replicas' words
-                        if ((need >> (4 * k)) & 0xFu) {
-                            const uint4 u = philox4x32_10((uint32_t)v, t, (uint32_t)(g0 + k), kStreamKsatSweep,
-                                                          C.key0, C.key1);
-                            const int b = 4 * k;
-                            flip |= (((need >> b) & 1u) && u.x < thr[b]) ? 1u << b : 0u;
-                            flip |= (((need >> (b + 1)) & 1u) && u.y < thr[b + 1]) ? 2u << b : 0u;
-                            flip |= (((need >> (b + 2)) & 1u) && u.z < thr[b + 2]) ? 4u << b : 0u;
-                            flip |= (((need >> (b + 3)) & 1u) && u.w < thr[b + 3]) ? 8u << b : 0u;
+                        // byte j: 128 + dE of replica j, from acc where its x is 1,
+                        // else the bytes' negatives (256 - b, 1 <= b <= 255)
+                        const uint32_t ones = spread4((xi >> (4 * k)) & 0xFu), m = (ones << 8) - ones;
+                        const uint32_t D = (acc[k] & m) | ((0x01010100u - acc[k]) & ~m);
+                        uint32_t thr[4];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            de[4 * k + j] = (int)((D >> (8 * j)) & 0xFFu) - 128;
+                            thr[j] = T[max(de[4 * k + j], 0)];
                         }
+                        // one generator call per group gives its 4 replicas' words
+                        PhiloxRounds u = {(uint32_t)v, t, (uint32_t)(g0 + k), kStreamKsatSweep, C.key0, C.key1};
+#pragma unroll
+                        for (int i = 0; i < 5; ++i)
+                            u.round2();
+                        const uint32_t w[4] = {u.c0, u.c1, u.c2, u.c3};
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            flip |= ((de[4 * k + j] <= 0) | (w[j] < thr[j])) ? 1u << (4 * k + j) : 0u;
                     }
+                    flip &= amask;
                     if (flip) {
                         n_acc += __builtin_popcount(flip);
                         const uint32_t nx = xi ^ flip;
@@ -395,8 +518,8 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
                     }
                 }
             }
-            __syncthreads();
         }
+        chunk_c = first_c;
 
         // sweep end: exact energies, best, first hit, snapshot
 #pragma unroll

@@ -28,4 +28,23 @@ __device__ __forceinline__ uint4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_
     return make_uint4(c0, c1, c2, c3);
 }
 
+// The same generator two rounds at a time, for counters that differ by lane
+// (the two xors of a word are one three-operand vector instruction), so that a
+// caller can spread its ten rounds over the waits of other work.
+struct PhiloxRounds {
+    uint32_t c0, c1, c2, c3, k0, k1;
+    __device__ __forceinline__ void round2() {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint64_t p0 = (uint64_t)c0 * 0xD2511F53u, p1 = (uint64_t)c2 * 0xCD9E8D57u;
+            c0 = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c1, k0, 0x96);
+            c2 = __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), c3, k1, 0x96);
+            c1 = (uint32_t)p1;
+            c3 = (uint32_t)p0;
+            k0 += 0x9E3779B9u;
+            k1 += 0xBB67AE85u;
+        }
+    }
+};
+
 }  // namespace nmc

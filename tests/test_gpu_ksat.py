@@ -342,3 +342,25 @@ def test_split_sweeps(n, k, alpha, R, cap):
     p.compare()
     p.anneal(np.full((1, 1), 2.0))
     p.compare()
+
+
+@pytest.mark.parametrize("n,k,alpha,R,cap,threads,reps", [
+    (1, 1, "1", 5, 0, 1024, 8), (5, 2, "2", 3, 0, 256, 4), (333, 4, "9.8", 13, 0, 512, 8),
+    (400, 4, "22", 9, 0, 256, 4), (700, 4, "9.5", 8, 1, 128, 4), (2049, 4, "9.8", 11, 65, 512, 8),
+    (2777, 3, "4.15", 6, 0, 256, 4), (16001, 3, "4.2", 5, 0, 1024, 4), (16001, 3, "4.2", 9, 1090, 512, 8),
+    (33000, 3, "2", 4, 0, 1024, 4)])
+def test_sweep_layout(n, k, alpha, R, cap, threads, reps):
+    """Sweeps of general workgroups: pairs of lanes that share clauses, odd
+    classes, a last chunk spread over lanes, more than 16 chunks in a class, short
+    blocks, addresses past 65,536, one and two groups per workgroup; integer
+    results, so exact."""
+    say(f"case: layout n={n} k={k} R={R} threads={threads} reps={reps}")
+    cp, lits = instances.gen_ksat(n, alpha, k, n)
+    p = KsatPair(n, cp, lits, R, n + 1, cap)
+    p.rep.set_tuning(threads)
+    p.rep.set_replicas_per_workgroup(reps)
+    p.anneal(instances.linear_schedule(0.1, 4.0, 6)[None, :], target=3)
+    p.compare()
+    host = (np.arange(n) % 3).astype(np.uint8)
+    p.anneal(np.stack([np.full(3, 3.0), np.zeros(3), np.full(3, 60.0)]), class_of=host)
+    p.compare()
