@@ -219,7 +219,8 @@ __device__ __forceinline__ uint32_t pack_counts(const uint32_t (&c)[4]) {
 // us per sweep; 4096 replicas of N = 20,000: 577 -> 490; 3-SAT N = 30,000, 512
 // replicas: 86 -> 71.  Tried: the generator's rounds spread over the slot loop
 // (263, small instances slower), one loop for whole and short blocks (copies of
-// the records in flight, 278), rows past a short block left out (263).
+// the records in flight: 255 where this loop took 240), rows past a short block
+// left out (263).
 template <int GPW>
 __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &R, const SweepCall &C, const int g,
                                             uint8_t *smem) {
