@@ -10,8 +10,10 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <map>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <numeric>
 #include <string>
@@ -261,26 +263,49 @@ struct nmc_instance {
 
 namespace {
 
-// fn(lo, hi) over [0, n) by host threads, each with 512 KB of work or more
-// (bytes_each per item); the caller takes the first share, and any that no
-// thread could be started for.  fn does not throw.
+// fn() on the caller's thread and on up to `threads` - 1 more (eight in all).  A
+// thread that cannot be started is done without, so fn takes its work from a
+// shared counter.  What an fn throws reaches the caller once all have ended.
 template <class F>
-void host_parallel(size_t n, size_t bytes_each, F fn) {
-    constexpr size_t grain = 512 * 1024, most = 8;
-    const size_t hw = std::max(1u, std::thread::hardware_concurrency());
-    const size_t parts = std::max<size_t>(1, std::min({most, hw, n, n * bytes_each / grain}));
+void run_workers(size_t threads, F fn) {
+    constexpr size_t most = 8;
+    std::mutex mu;
+    std::exception_ptr error;
+    auto guarded = [&]() noexcept {
+        try {
+            fn();
+        } catch (...) {
+            const std::lock_guard<std::mutex> hold(mu);
+            error = std::current_exception();
+        }
+    };
     std::thread pool[most];
     size_t started = 1;
     try {
-        for (; started < parts; ++started)
-            pool[started] = std::thread(fn, n * started / parts, n * (started + 1) / parts);
+        for (; started < std::min(threads, most); ++started)
+            pool[started] = std::thread(guarded);
     } catch (...) {  // (no thread, or no memory for one)
     }
-    fn((size_t)0, n / parts);
-    if (started < parts)
-        fn(n * started / parts, n);
+    guarded();
     for (size_t k = 1; k < started; ++k)
         pool[k].join();
+    if (error)
+        std::rethrow_exception(error);
+}
+
+size_t host_threads() { return std::max(1u, std::thread::hardware_concurrency()); }
+
+// fn(lo, hi) over [0, n) by host threads, each with 512 KB of work or more
+// (bytes_each per item).
+template <class F>
+void host_parallel(size_t n, size_t bytes_each, F fn) {
+    constexpr size_t grain = 512 * 1024, most = 8;
+    const size_t parts = std::max<size_t>(1, std::min({most, host_threads(), n, n * bytes_each / grain}));
+    std::atomic<size_t> next{0};
+    run_workers(parts, [&] {
+        for (size_t k; (k = next.fetch_add(1)) < parts;)
+            fn(n * k / parts, n * (k + 1) / parts);
+    });
 }
 
 // Greedy colouring: variables in index order take the smallest colour that
@@ -643,15 +668,7 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
                 for (size_t i; (i = next.fetch_add(1)) < work.size();)
                     schedule_chunk(work[i].lanes, work[i].nslot, bank_schedule, work[i].placed, dummy);
             };
-            const size_t n_rec = vcl.size();
-            const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
-            const unsigned nt = bank_schedule && n_rec >= 20000 ? std::min(8u, hw) : 1u;
-            std::vector<std::thread> pool;
-            for (unsigned t = 1; t < nt; ++t)
-                pool.emplace_back(worker);
-            worker();
-            for (auto &t : pool)
-                t.join();
+            run_workers(bank_schedule && vcl.size() >= 20000 ? host_threads() : 1, worker);
         }
         rec.resize((size_t)slot_rows * kChunk);
         for (size_t i = 0; i < work.size(); ++i) {
@@ -737,14 +754,7 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
                 for (size_t i; (i = next.fetch_add(1)) < work.size();)
                     schedule_chunk(work[i].lanes, 2 * sp_info[i].y, bank_schedule, work[i].placed, dummy);
             };
-            const unsigned nt =
-                bank_schedule && vcl.size() >= 20000 ? std::min(8u, std::max(1u, std::thread::hardware_concurrency())) : 1u;
-            std::vector<std::thread> pool;
-            for (unsigned t = 1; t < nt; ++t)
-                pool.emplace_back(worker);
-            worker();
-            for (auto &t : pool)
-                t.join();
+            run_workers(bank_schedule && vcl.size() >= 20000 ? host_threads() : 1, worker);
             sp_rec.resize((size_t)rows * kChunk * 2);
             for (size_t i = 0; i < work.size(); ++i)
                 for (int32_t sl = 0; sl < 2 * sp_info[i].y; ++sl)
@@ -887,14 +897,7 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
                     work[i] = SweepChunk();
                 }
             };
-            const unsigned nt =
-                bank_schedule && vcl.size() >= 20000 ? std::min(8u, std::max(1u, std::thread::hardware_concurrency())) : 1u;
-            std::vector<std::thread> pool;
-            for (unsigned t = 1; t < nt; ++t)
-                pool.emplace_back(worker);
-            worker();
-            for (auto &t : pool)
-                t.join();
+            run_workers(bank_schedule && vcl.size() >= 20000 ? host_threads() : 1, worker);
         }
         // wide layout: per incidence (var_ptr order) the clause's other
         // literals as spin-table rows (v for x_v, n + 1 + v for NOT x_v, row

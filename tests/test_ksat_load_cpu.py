@@ -1,0 +1,33 @@
+"""Loading k-SAT instances on the host: layouts, threads, limits."""
+import subprocess
+import sys
+
+import pytest
+
+ROOT = __file__.rsplit("/", 2)[0]
+
+FEW_THREADS = """
+import ctypes, resource, sys
+sys.path.insert(0, {root!r})
+from paper_2111_13628_amd import instances, nmc
+nmc.lib()
+cp, lits = instances.gen_ksat({n}, "9.8", 4, 7)
+# stacks of 1 GiB: the address space left has room for {room} of them
+libc = ctypes.CDLL(None)
+attr = ctypes.create_string_buffer(64)
+assert libc.pthread_attr_init(attr) == 0
+assert libc.pthread_attr_setstacksize(attr, ctypes.c_size_t(1 << 30)) == 0
+assert libc.pthread_setattr_default_np(attr) == 0
+used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + ({room} << 30) + (900 << 20), -1))
+print("loaded", nmc.Instance.ksat({n}, cp, lits).info.n_items)
+"""
+
+
+@pytest.mark.parametrize("n,room", [(300, 0), (5000, 0), (5000, 2), (30000, 0), (30000, 3)])
+def test_load_with_few_threads(n, room):
+    """Records are placed by several threads from some size on; with room for
+    none or only a few of them, the threads there are do all of the work."""
+    r = subprocess.run([sys.executable, "-c", FEW_THREADS.format(root=ROOT, n=n, room=room)], capture_output=True,
+                       text=True, timeout=300)
+    assert r.returncode == 0 and f"loaded {n}" in r.stdout, (r.returncode, r.stderr[-500:])
