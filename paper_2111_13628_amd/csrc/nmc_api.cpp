@@ -755,7 +755,7 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
                     schedule_chunk(work[i].lanes, 2 * sp_info[i].y, bank_schedule, work[i].placed, dummy);
             };
             run_workers(bank_schedule && vcl.size() >= 20000 ? host_threads() : 1, worker);
-            sp_rec.resize((size_t)rows * kChunk * 2);
+            sp_rec.resize((size_t)(rows + kSplitAhead) * kChunk * 2);  // (the last chunk's reads ahead end in zeros)
             for (size_t i = 0; i < work.size(); ++i)
                 for (int32_t sl = 0; sl < 2 * sp_info[i].y; ++sl)
                     for (int lane = 0; lane < kChunk; ++lane)
@@ -875,7 +875,7 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
             }
             const ChunkRec dummy{{ONES, ZERO, ZERO}, 0u};
             std::atomic<size_t> next{0};
-            bl_rec.resize((size_t)bytes / 4);
+            bl_rec.resize(((size_t)bytes + kBlockBytes) / 4);  // (a short last block is read whole)
             auto worker = [&] {
                 for (size_t i; (i = next.fetch_add(1)) < work.size();) {
                     const int4 f = bl_info[i];

@@ -54,6 +54,8 @@ constexpr int kBlockSign = kChunk * 4, kBlockRow = kChunk * 16, kBlockBytes = kB
 // classes hold kSplitMaxClass variables or fewer on average.
 constexpr int kSplitMaxVars = 12288;
 constexpr int kSplitMaxClass = 256;
+// pair-rows read ahead from a chunk's first one (fewer on 8 and 16 lanes)
+constexpr int kSplitAhead = 6;
 
 // LDS available to one workgroup on gfx950.
 constexpr size_t kLdsBytes = 160 * 1024;

@@ -293,7 +293,7 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
     __syncthreads();
 
     uint32_t n_acc = 0;  // flips this lane accepted in this call
-    // the instance's records (out-of-range offsets would read zeros)
+    // the instance's records, with room for the reads ahead of the last chunk
     const __amdgpu_buffer_rsrc_t recs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(I.bl_rec), 0, (int)I.bl_rec_bytes, kBufferWord3);
     auto sign_at = [&](int at) { return __builtin_amdgcn_raw_buffer_load_b32(recs, lane * 4, at, 0); };
@@ -339,8 +339,8 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
             next_h = first_h;
         next = scalar_read(infos, next_h);
     };
-    // a block, with what follows one shorter than 8 slots (zeros past the end:
-    // out of the buffer's bounds); not used
+    // a block, with what follows one shorter than 8 slots (after the last one
+    // zeros); not used
     auto read_block = [&](int at) {
         sign = (uint32_t)sign_at(at);
 #pragma unroll
@@ -659,7 +659,7 @@ __global__ void __launch_bounds__(1024) ksat_split_kernel(KsatDev I, KsatRepDev 
     extern __shared__ __align__(16) uint8_t smem[];
     constexpr int PER = kChunk >> LG;  // variables of a chunk
     // record pairs of the next chunk loaded ahead: 48 clauses per variable
-    constexpr int PRE = LG == 2 ? 6 : LG == 3 ? 4 : 3;
+    constexpr int PRE = LG == 2 ? kSplitAhead : LG == 3 ? 4 : 3;
     const int n = I.n, g = blockIdx.x;
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, nwaves = nthr >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -723,8 +723,8 @@ __global__ void __launch_bounds__(1024) ksat_split_kernel(KsatDev I, KsatRepDev 
             uint4, __builtin_amdgcn_raw_buffer_load_b128(recs, lane * 16, row * (kChunk * 16), 0));
     };
     // loads of the chunk of entry e: lane words and the first records (rows
-    // past the chunk are other chunks' or, past the end, zeros; they are not
-    // used)
+    // past the chunk are other chunks' or, after the last one, zeros; they are
+    // not used)
     auto fetch = [&](const int4 &x) {
         e = make_int4(__builtin_amdgcn_readfirstlane(x.x), __builtin_amdgcn_readfirstlane(x.y),
                       __builtin_amdgcn_readfirstlane(x.z), __builtin_amdgcn_readfirstlane(x.w));

@@ -2,7 +2,10 @@
 import subprocess
 import sys
 
+import numpy as np
 import pytest
+
+from paper_2111_13628_amd import nmc
 
 ROOT = __file__.rsplit("/", 2)[0]
 
@@ -31,3 +34,14 @@ def test_load_with_few_threads(n, room):
     r = subprocess.run([sys.executable, "-c", FEW_THREADS.format(root=ROOT, n=n, room=room)], capture_output=True,
                        text=True, timeout=300)
     assert r.returncode == 0 and f"loaded {n}" in r.stdout, (r.returncode, r.stderr[-500:])
+
+
+@pytest.mark.parametrize("n", [1, 3])
+def test_reads_ahead_stay_inside(n):
+    """The sweeps read a whole block of 8 slots (256 + 4 x 1024 bytes), the split
+    sweeps six rows of 1024 bytes, from the last chunk's first one on, however
+    few slots the chunk has: both record arrays hold that."""
+    cp = np.arange(n + 1, dtype=np.int32)
+    inst = nmc.Instance.ksat(n, cp, np.arange(1, n + 1, dtype=np.int32))
+    per_class = 256 + 1024 + 1024  # the shortest chunk in either layout
+    assert inst.footprint(1)[0] >= 256 + 4 * 1024 + 6 * 1024 + per_class
