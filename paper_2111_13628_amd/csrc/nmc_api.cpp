@@ -188,7 +188,6 @@ struct nmc_instance {
     // clauses' literal addresses in that order and each clause's position
     size_t off_lbp_caddr = 0, off_lbp_pos = 0;
     std::vector<int32_t> lbp_pos;
-    uint32_t rec_bytes = 0;  // size of the record array
     // split layout (see KsatDev)
     size_t off_sp_rec = 0, off_sp_var = 0, off_sp_info = 0, off_sp_color = 0;
     uint32_t sp_rec_bytes = 0;
@@ -218,7 +217,6 @@ struct nmc_instance {
     KsatDev ksat_dev() const {
         KsatDev d{};
         d.rec = reinterpret_cast<const uint64_t *>(dev + off_rec);
-        d.rec_bytes = rec_bytes;
         d.chunk_var = reinterpret_cast<const int32_t *>(dev + off_chunk_var);
         d.chunk_info = reinterpret_cast<const int2 *>(dev + off_chunk_info);
         d.color_chunk = reinterpret_cast<const int32_t *>(dev + off_color_chunk);
@@ -783,7 +781,11 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
                 std::vector<ChunkRec> placed[2];
             };
             std::vector<SweepChunk> work;
-            int32_t bytes = 0;  // (below 2^31: N <= 65534 and degree <= 127)
+            // a variable alone in its chunk has 66 slots at most, and 64 share
+            // 128: byte offsets stay below 2^32, and not below 2^31
+            constexpr uint64_t most = 9 * kBlockSign + 33 * kBlockRow;
+            static_assert(2 * most >= 16 * kBlockSign + 64 * kBlockRow && kMaxVars * most + kBlockBytes <= UINT32_MAX);
+            uint32_t bytes = 0;
             auto deg = [&](int32_t v) { return vptr[v + 1] - vptr[v]; };
             auto even = [](int32_t x) { return (x + 1) / 2 * 2; };
             auto rec_of = [&](int32_t q) {
@@ -803,8 +805,8 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
                 return v | (int32_t)((uint32_t)(slots - neg) << 20);
             };
             auto add_chunk = [&](SweepChunk &&w, int32_t nslot, int32_t lg, int32_t ws) {
-                bl_info.push_back(make_int4(bytes, nslot, lg, ws));
-                bytes += (nslot + 7) / 8 * kBlockSign + nslot / 2 * kBlockRow;
+                bl_info.push_back(make_int4((int32_t)bytes, nslot, lg, ws));
+                bytes += (uint32_t)((nslot + 7) / 8 * kBlockSign + nslot / 2 * kBlockRow);
                 work.push_back(std::move(w));
             };
             for (int32_t c = 0; c < ncol; ++c) {
@@ -883,7 +885,7 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
                     schedule_chunk(work[i].lanes[0], ws, bank_schedule, work[i].placed[0], dummy, true);
                     schedule_chunk(work[i].lanes[1], nslot - ws, bank_schedule, work[i].placed[1], dummy, true);
                     for (int32_t sl = 0; sl < nslot; ++sl) {
-                        uint32_t *block = bl_rec.data() + (size_t)(f.x + sl / 8 * kBlockBytes) / 4;
+                        uint32_t *block = bl_rec.data() + ((uint32_t)f.x + (uint32_t)(sl / 8 * kBlockBytes)) / 4;
                         const int last = std::min(nslot, (sl / 8 + 1) * 8) - 1;
                         for (int lane = 0; lane < kChunk; ++lane) {
                             const ChunkRec &r = sl < ws ? work[i].placed[0][(size_t)sl * kChunk + lane]
@@ -953,7 +955,6 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
 
         Arena ar;
         I->off_rec = ar.take(rec.size() * 8);
-        I->rec_bytes = (uint32_t)(rec.size() * 8);  // below 2^31: N <= 65534 and degree <= 127
         I->off_chunk_var = ar.take(chunk_var.size() * 4);
         I->off_chunk_info = ar.take(chunk_info.size() * 8);
         I->off_color_chunk = ar.take(color_chunk.size() * 4);

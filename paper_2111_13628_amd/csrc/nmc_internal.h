@@ -75,7 +75,6 @@ struct KsatDev {
     const uint32_t *lbp_caddr;   // [M][4] clause_addr in the LBP clause order (clauses by smallest variable)
     const int32_t *lbp_pos;      // [M] position of each clause in the LBP clause order
     int32_t n, m, n_colors, n_chunks, dmax;
-    uint32_t rec_bytes;          // size of rec in bytes (the bound of buffer loads)
     // split layout (small colour classes; sp_lg = 0: none): each variable on
     // 2^sp_lg lanes in every chunk, records in 16-byte pairs of slots
     const uint64_t *sp_rec;      // [pair-row][64 lanes][2]
@@ -91,7 +90,7 @@ struct KsatDev {
     // pairs, 16 bytes a lane; the last block holds 2, 4, 6 or 8 slots
     const uint32_t *bl_rec;      // [block]([64 lanes], [pair][64 lanes][2 records of 8 bytes])
     const int32_t *bl_var;       // [chunk][64] variable | share of the closed form << 20, -1: decides nothing
-    const int4 *bl_info;         // [chunk] (byte offset in bl_rec, slots, lg, slots of an odd lane's own variable)
+    const int4 *bl_info;         // [chunk] (byte offset in bl_rec, unsigned, slots, lg, slots of an odd lane's own variable)
     const int32_t *bl_color;     // [n_colors + 1] chunk range of each colour class
     uint32_t bl_rec_bytes;
     // wide layout (wide != 0; rec and the chunk arrays are then empty)

@@ -296,10 +296,10 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
     // the instance's records, with room for the reads ahead of the last chunk
     const __amdgpu_buffer_rsrc_t recs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(I.bl_rec), 0, (int)I.bl_rec_bytes, kBufferWord3);
-    auto sign_at = [&](int at) { return __builtin_amdgcn_raw_buffer_load_b32(recs, lane * 4, at, 0); };
-    auto row_at = [&](int at, int row) -> uint4 {
-        return __builtin_bit_cast(
-            uint4, __builtin_amdgcn_raw_buffer_load_b128(recs, lane * 16, at + kBlockSign + row * kBlockRow, 0));
+    auto sign_at = [&](uint32_t at) { return __builtin_amdgcn_raw_buffer_load_b32(recs, lane * 4, (int)at, 0); };
+    auto row_at = [&](uint32_t at, int row) -> uint4 {
+        const uint32_t to = at + (uint32_t)(kBlockSign + row * kBlockRow);
+        return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(recs, lane * 16, (int)to, 0));
     };
     // the four waves of a SIMD at four priorities: chunks of one length would
     // otherwise all gather, then all decide (264 -> 257 us per sweep)
@@ -341,7 +341,7 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
     };
     // a block, with what follows one shorter than 8 slots (after the last one
     // zeros); not used
-    auto read_block = [&](int at) {
+    auto read_block = [&](uint32_t at) {
         sign = (uint32_t)sign_at(at);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -351,7 +351,7 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
     if (first_c < I.n_colors) {
         info = scalar_read(infos, first_h);
         lane_word = lane_words(first_h);
-        read_block(info.x);
+        read_block((uint32_t)info.x);
         advance();
     }
     for (int s = 0; s < C.n_sweeps; ++s) {
@@ -415,7 +415,8 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
                     for (int k = 0; k < GPW; ++k)
                         word[k] = 0;
                 };
-                int left = nslot, at = info.x;
+                int left = nslot;
+                uint32_t at = (uint32_t)info.x;
                 for (; left > 8; left -= 8) {
                     at += kBlockBytes;
                     const uint32_t sg = sign;
@@ -457,7 +458,7 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
                 count(sign, nslot - ws);
                 // on to the next chunk, while this one is decided
                 info = next;
-                read_block(info.x);
+                read_block((uint32_t)info.x);
                 lane_word = lane_words(next_h);
                 chunk_c = next_c;
                 advance();

@@ -364,3 +364,23 @@ def test_sweep_layout(n, k, alpha, R, cap, threads, reps):
     host = (np.arange(n) % 3).astype(np.uint8)
     p.anneal(np.stack([np.full(3, 3.0), np.zeros(3), np.full(3, 60.0)]), class_of=host)
     p.compare()
+
+
+def test_sweep_records_past_2_gib(monkeypatch):
+    """65,534 variables of degree 127, one per class and one lane each: the sweep
+    records take 2.37 GB, so their byte offsets need all 32 bits; integer
+    results, so exact."""
+    say("case: sweep records past 2 GiB")
+    monkeypatch.setenv("NMC_KSAT_SPLIT", "0")
+    monkeypatch.setenv("NMC_KSAT_BANK_SCHEDULE", "0")  # (seconds of placement; results do not depend on it)
+    n = 65534
+    rng, v = np.random.default_rng(SEED), np.arange(n)
+    # every variable once in each place of 31 clauses of 4 and of one of 3
+    rows = [np.stack([(v + s) % n for s in (0, *rng.choice(np.arange(1, n), k - 1, replace=False))], 1)
+            for k in [4] * 31 + [3]]
+    lits = np.concatenate([r.reshape(-1) for r in rows]) + 1
+    lits = (lits * rng.choice([-1, 1], lits.size)).astype(np.int32)
+    cp = np.concatenate([[0], np.cumsum(np.repeat([4] * 31 + [3], n))]).astype(np.int32)
+    p = KsatPair(n, cp, lits, 5, SEED, 1)
+    p.anneal(np.array([[0.5, 3.0]]))
+    p.compare()
