@@ -696,10 +696,17 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
         std::vector<uint64_t> sp_rec;
         std::vector<int32_t> sp_color(ncol + 1, 0);
         std::vector<int2> sp_info, sp_var;
-        if (!I->wide && split && n <= kSplitMaxVars && (int64_t)n <= (int64_t)kSplitMaxClass * ncol) {
-            int32_t lg = 2;
-            while (lg < kMaxSplitLog && ((int64_t)n << (lg + 1)) <= (int64_t)256 * ncol)
-                ++lg;
+        int32_t lg = 2, split_chunks = 0, split_waves = 0;
+        while (lg < kMaxSplitLog && ((int64_t)n << (lg + 1)) <= (int64_t)256 * ncol)
+            ++lg;
+        for (int32_t c = 0; c < ncol; ++c) {
+            const int32_t k = ((I->color_ptr[c + 1] - I->color_ptr[c]) + (kChunk >> lg) - 1) / (kChunk >> lg);
+            split_chunks += k;
+            split_waves = std::max(split_waves, std::min(16, k));
+        }
+        // (only where a sweep with one threshold row fits in LDS)
+        if (!I->wide && split && (int64_t)n <= (int64_t)kSplitMaxClass * ncol &&
+            ksat_split_lds_bytes(n, ncol, split_chunks, lg, dmax + 1, split_waves) <= kLdsBytes) {
             const int32_t L = 1 << lg, per = kChunk >> lg;
             struct SplitChunk {
                 std::vector<std::vector<ChunkRec>> lanes;
@@ -744,7 +751,6 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
                     }
                 }
                 sp_color[c + 1] = (int32_t)sp_info.size();
-                I->sp_waves = std::max(I->sp_waves, std::min(16, sp_color[c + 1] - sp_color[c]));
             }
             const ChunkRec dummy{{ONES, ZERO, ZERO}, 0u};
             std::atomic<size_t> next{0};
@@ -760,7 +766,8 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
                         sp_rec[(size_t)(sp_info[i].x + sl / 2) * 2 * kChunk + (size_t)lane * 2 + (sl & 1)] =
                             pack_rec(work[i].placed[(size_t)sl * kChunk + lane]);
             I->sp_lg = lg;
-            I->sp_chunks = (int32_t)sp_info.size();
+            I->sp_chunks = split_chunks;
+            I->sp_waves = split_waves;
         }
         // sweep layout: chunks of one class with lengths as equal as possible,
         // since a class ends when its longest wave does.  A class of K chunks

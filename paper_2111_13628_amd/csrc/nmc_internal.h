@@ -50,9 +50,9 @@ constexpr int kMaxSplitLog = 4;
 constexpr int kLayoutWaves = 16;
 constexpr int kBlockSign = kChunk * 4, kBlockRow = kChunk * 16, kBlockBytes = kBlockSign + 4 * kBlockRow;
 
-// The split layout: instances of at most kSplitMaxVars variables whose colour
-// classes hold kSplitMaxClass variables or fewer on average.
-constexpr int kSplitMaxVars = 12288;
+// The split layout: instances whose colour classes hold kSplitMaxClass
+// variables or fewer on average and whose split sweeps fit in LDS (some 15
+// bytes per variable and 16 per class and wave: up to N of 9,000 to 9,600 or so).
 constexpr int kSplitMaxClass = 256;
 // pair-rows read ahead from a chunk's first one (fewer on 8 and 16 lanes)
 constexpr int kSplitAhead = 6;
@@ -253,6 +253,7 @@ hipError_t launch_set_status(const SetStatusSrc *src, SetStatus *out, int n_sets
 
 // ---- launchers (nmc_ksat.hip) ----
 size_t ksat_sweep_lds_bytes(int n, int n_classes, int stride);
+size_t ksat_split_lds_bytes(int n, int n_colors, int n_chunks, int lg, int tab_words, int waves);
 hipError_t ksat_launch_init(const KsatDev &I, const KsatRepDev &R, uint32_t key0, uint32_t key1, hipStream_t s);
 hipError_t ksat_launch_wide_pack(const KsatDev &I, const KsatRepDev &R, bool unpack, hipStream_t s);
 // energies of every replica of a wide instance from its group-major state

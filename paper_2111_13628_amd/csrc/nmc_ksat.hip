@@ -1084,6 +1084,10 @@ size_t ksat_sweep_lds_bytes(int n, int n_classes, int stride) {
     return align_up(2 * (size_t)n + 2, 16) + align_up((size_t)n_classes * stride, 4) * 4 + 16 * sizeof(int);
 }
 
+size_t ksat_split_lds_bytes(int n, int n_colors, int n_chunks, int lg, int tab_words, int waves) {
+    return split_lds(n, n_colors, n_chunks, lg, tab_words, waves).total;
+}
+
 hipError_t launch_set_status(const SetStatusSrc *src, SetStatus *out, int n_sets, hipStream_t s) {
     hipLaunchKernelGGL(set_status_kernel, dim3(n_sets), dim3(256), 0, s, src, out);
     return hipGetLastError();
@@ -1143,7 +1147,7 @@ hipError_t ksat_launch_sweep(const KsatDev &I, const KsatRepDev &R, const SweepC
     if (attr_split != hipSuccess)
         return attr_split;
     const size_t split =
-        I.sp_lg ? split_lds(I.n, I.n_colors, I.sp_chunks, I.sp_lg, C.n_classes * C.stride, I.sp_waves).total : 0;
+        I.sp_lg ? ksat_split_lds_bytes(I.n, I.n_colors, I.sp_chunks, I.sp_lg, C.n_classes * C.stride, I.sp_waves) : 0;
     if (C.gpw == 2)
         hipLaunchKernelGGL(ksat_sweep_kernel<2>, dim3((R.n_groups + 1) / 2), dim3(block_threads), lds, s, I, R, C);
     // (also with more groups than CUs: 4096 replicas of n = 200, 1000, 5000, 9000

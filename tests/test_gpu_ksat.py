@@ -384,3 +384,16 @@ def test_sweep_records_past_2_gib(monkeypatch):
     p = KsatPair(n, cp, lits, 5, SEED, 1)
     p.anneal(np.array([[0.5, 3.0]]))
     p.compare()
+
+
+@pytest.mark.parametrize("n", [9500, 9700])
+def test_split_layout_limit(n):
+    """Classes of 150 variables: the largest instances whose split sweeps fit in
+    LDS and the first that take the general ones; integer results, so exact."""
+    say(f"case: split limit n={n}")
+    cp, lits = instances.gen_ksat(n, "9.8", 4, n)
+    p = KsatPair(n, cp, lits, 6, n + 1, 150)
+    p.anneal(instances.linear_schedule(0.1, 4.0, 5)[None, :], target=3)
+    p.compare()
+    p.anneal(np.stack([np.full(3, 3.0), np.zeros(3), np.full(3, 60.0)]), class_of=(np.arange(n) % 3).astype(np.uint8))
+    p.compare()

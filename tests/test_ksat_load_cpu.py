@@ -5,7 +5,7 @@ import sys
 import numpy as np
 import pytest
 
-from paper_2111_13628_amd import nmc
+from paper_2111_13628_amd import instances, nmc
 
 ROOT = __file__.rsplit("/", 2)[0]
 
@@ -45,3 +45,17 @@ def test_reads_ahead_stay_inside(n):
     inst = nmc.Instance.ksat(n, cp, np.arange(1, n + 1, dtype=np.int32))
     per_class = 256 + 1024 + 1024  # the shortest chunk in either layout
     assert inst.footprint(1)[0] >= 256 + 4 * 1024 + 6 * 1024 + per_class
+
+
+def test_split_layout_only_where_it_fits():
+    """Classes of 150 variables: up to 9,500 variables the split layout is a
+    second set of records beside the sweep layout's; at 10,000 no split sweep
+    fits in LDS, so there is none, as at 13,000."""
+
+    def per_variable(n):
+        cp, lits = instances.gen_ksat(n, "9.8", 4, n)
+        return nmc.Instance.ksat(n, cp, lits, 150).footprint(1)[0] / n
+
+    large = per_variable(13000)
+    assert per_variable(9500) > 1.2 * large
+    assert per_variable(10000) < 1.05 * large
