@@ -198,3 +198,13 @@ def test_full_size_qap_tempering_sampled_chains():
     assert (rep.get_state("best")[sl] == orep.best_perm[sl]).all()
     assert (be["energy"][sl] == orep.cost[sl]).all()
     assert (be["best_per_replica"][sl] == orep.best[sl]).all()
+
+
+def test_qap_tempering_sixteen_waves():
+    """2112 replicas of n = 150 at 33 temperatures of 64 chains: workgroups of 16
+    waves, four temperatures each; integer results, so exact."""
+    say("case: QAP tempering n=150 R=2112")
+    F, D = instances.gen_qap(150, 5)
+    pair = QapPair(F, D, 2112, 23)
+    pair.pt_run(np.geomspace(2e-6, 2e-4, 33), 2, 1, 1)
+    pair.compare()

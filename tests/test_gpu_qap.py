@@ -253,3 +253,44 @@ def test_qap_row_sweeps(n, R, hi, monkeypatch):
         cls = p.backbone(2, 3)
         p.anneal(reanneal_profile(2, sc), profile="backbone", class_of=cls)
         p.compare()
+
+
+@pytest.mark.parametrize("n,R,hi,S", [(150, 2100, 60, 2), (193, 6, 200, 3), (200, 1100, 60, 2), (230, 1040, 50, 1)])
+def test_qap_row_sweeps_wide_workgroups(n, R, hi, S, monkeypatch):
+    """Sixteen waves per workgroup (n = 150, more than 2048 replicas), eight above
+    n = 192, and an instance whose table leaves no room for row sweeps (n = 193,
+    entries to 200: the stepped kernel, chosen per sweep and with whole rows
+    asked for); integer results, so exact."""
+    F, D = instances.gen_qap(n, SEED + 7 * n, 0, hi)
+    sc = beta_scale(F, D, samples=300)
+    for rows in ("16", "0"):
+        say(f"case: qap rows={rows} n={n} R={R}")
+        monkeypatch.setenv("NMC_QAP_ROWS", rows)
+        p = QapPair(F, D, R, SEED + n)
+        p.anneal(np.geomspace(0.3 * sc, 8.0 * sc, S)[None, :], target=0)
+        p.anneal(np.full((1, 1), 3.0 * sc))
+        p.compare()
+
+
+@pytest.mark.parametrize("n,hi", [(65, 99), (100, 99), (150, 60), (193, 40), (230, 20)])
+def test_qap_batched_row_sweeps(n, hi, monkeypatch):
+    """A batched launch beside a small set: 16 waves per workgroup at every
+    operand size (the last one does not fit and takes the stepped kernel), whole
+    rows pinned and chosen per sweep; integer results, so exact."""
+    F, D = instances.gen_qap(n, SEED + 9 * n, 0, hi)
+    sc = beta_scale(F, D, samples=300)
+    F2, D2 = instances.gen_qap(30, SEED, 0, hi)
+    for rows in ("16", "0"):
+        say(f"case: qap batch rows={rows} n={n}")
+        monkeypatch.setenv("NMC_QAP_ROWS", rows)
+        pairs = [QapPair(F, D, 21, SEED + n), QapPair(F2, D2, 50, SEED + 1)]
+        b = nmc.Batch([p.rep for p in pairs])
+        beta = np.geomspace(0.05 * sc, 8.0 * sc, 5)[None, :]
+        hot = reanneal_profile(2, sc)
+        b.anneal(beta, targets=0)
+        b.estimate_backbone(2, 3, False)
+        b.anneal(hot, "backbone")
+        for p in pairs:
+            p.orep.anneal(beta, target=0)
+            p.orep.anneal(hot, class_of=p.orep.backbone(2, 3)[0])
+            p.compare()
