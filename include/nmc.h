@@ -472,9 +472,9 @@ int nmc_set_replicas_per_workgroup(nmc_replicas *rep, int32_t reps);
 int nmc_get_tuning(const nmc_replicas *rep, int32_t *block_threads, int32_t *reps_per_workgroup);
 
 /* Tunes one k-SAT replica set: times probe_sweeps sweeps on a copy of its
- * states (the set does not move) for every workgroup size (64 .. 1024) and
- * then 4 or 8 replicas per workgroup (nmc_batch_tune on a batch of this one
- * set), keeps the fastest and returns it (outputs optional).
+ * states (the set does not move), by the launch that nmc_anneal would make,
+ * for every workgroup size (64 .. 1024) and then 4 or 8 replicas per
+ * workgroup, keeps the fastest and returns it (outputs optional).
  * Errors: INVALID, UNSUPPORTED (QAP), DEVICE. */
 int nmc_tune(nmc_replicas *rep, int32_t probe_sweeps, int32_t *block_threads, int32_t *reps_per_workgroup,
              void *stream);

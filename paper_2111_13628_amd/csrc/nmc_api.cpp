@@ -3983,21 +3983,86 @@ extern "C" int nmc_tune(nmc_replicas *P, int32_t probe_sweeps, int32_t *block_th
             *reps_per_workgroup = 0;
         return ok();
     }
-    nmc_batch *B = nullptr;
-    int rc = nmc_batch_create(&P, 1, &B);
-    if (rc)
-        return rc;
-    int32_t chosen = 0;
-    rc = nmc_batch_tune(B, probe_sweeps, &chosen, stream);
-    nmc_batch_free(B);
-    if (rc)
-        return rc;
-    P->block_threads = chosen;
-    if (block_threads)
-        *block_threads = P->block_threads;
-    if (reps_per_workgroup)
-        *reps_per_workgroup = P->gpw * kGroup;
-    return ok();
+    if (probe_sweeps < 1 || probe_sweeps > 1000)
+        return fail(NMC_ERR_INVALID, "probe_sweeps must be in [1, 1000]");
+    if (!P->inst->dev)
+        return fail(NMC_ERR_STATE, "instance is not bound");
+    try {
+        hipStream_t s = as_stream(stream);
+        // a copy of the set, released on every exit
+        struct Guard {
+            hipStream_t s;
+            uint8_t *scratch = nullptr;
+            nmc_replicas clone;
+            ~Guard() {
+                if (scratch) {
+                    (void)hipStreamSynchronize(s);
+                    (void)hipFree(scratch);
+                }
+                if (clone.tab_dev)
+                    (void)hipFree(clone.tab_dev);
+            }
+        } guard{s};
+        HIP_OR_FAIL(hipMalloc(&guard.scratch, P->bytes));
+        HIP_OR_FAIL(hipMemcpyAsync(guard.scratch, P->dev, P->bytes, hipMemcpyDeviceToDevice, s));
+        guard.clone = rebased(P, guard.scratch);
+        nmc_replicas &C = guard.clone;
+        C.profiling = true;
+        const std::vector<double> beta((size_t)probe_sweeps, 1.0);
+        // kernel time of probe_sweeps sweeps by the launch that the set would
+        // make (the shorter of two; the copy's states move on)
+        auto time_config = [&](int block, int gpw, double *ms) -> int {
+            C.block_threads = block;
+            C.gpw = gpw;
+            for (int rep = 0; rep < 2; ++rep) {
+                C.sweeps_done = 0;
+                C.prof_ms = 0;
+                if (int rc = anneal_impl(&C, beta.data(), 1, probe_sweeps, NMC_PROFILE_HOMOGENEOUS, nullptr, -1, stream))
+                    return rc;
+                *ms = rep == 0 ? C.prof_ms : std::min(*ms, C.prof_ms);
+            }
+            return NMC_OK;
+        };
+        // the workgroup size with 4 replicas per workgroup (1024: the split
+        // sweeps where the set has them), then 8 at the best general size
+        int best_b = 0, general_b = 0, best_g = 1;
+        double best_ms = 0, general_ms = 0;
+        SweepCall probe{};
+        probe.n_classes = 1;
+        probe.stride = P->inst->dmax + 1;
+        probe.gpw = 1;
+        for (int cand : {64, 128, 256, 512, 1024}) {
+            double ms = 0;
+            if (int rc = time_config(cand, 1, &ms))
+                return rc;
+            if (best_b == 0 || ms < best_ms) {
+                best_b = cand;
+                best_ms = ms;
+            }
+            if (!ksat_takes_split(P->inst->ksat_dev(), probe, cand) && (general_b == 0 || ms < general_ms)) {
+                general_b = cand;
+                general_ms = ms;
+            }
+        }
+        if (P->G > 1) {
+            double ms = 0;
+            if (int rc = time_config(general_b, 2, &ms))
+                return rc;
+            if (ms < 0.99 * best_ms) {
+                best_b = general_b;
+                best_g = 2;
+            }
+        }
+        P->block_threads = best_b;
+        P->gpw = best_g;
+        if (block_threads)
+            *block_threads = P->block_threads;
+        if (reps_per_workgroup)
+            *reps_per_workgroup = P->gpw * kGroup;
+        return ok();
+    } catch (const std::bad_alloc &) {
+        return fail(NMC_ERR_CAPACITY, "host allocation failed");
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -1122,6 +1122,22 @@ hipError_t ksat_launch_reset_tallies(const KsatRepDev &R, int n, hipStream_t s) 
     return hipMemcpyAsync(R.best_xs, R.xs, (size_t)R.n_groups * n, hipMemcpyDeviceToDevice, s);
 }
 
+static size_t split_lds_of(const KsatDev &I, const SweepCall &C) {
+    return ksat_split_lds_bytes(I.n, I.n_colors, I.sp_chunks, I.sp_lg, C.n_classes * C.stride, I.sp_waves);
+}
+
+// At the default workgroup size, where the layout exists and its sweep fits in
+// LDS.  Up to one group per CU (1024 replicas) no general workgroup of 64 to
+// 1024 threads with 4 or 8 replicas is faster: 4-SAT n = 200, 1000, 5000, 9000
+// 17, 24, 47, 64 us per sweep against 34, 67, 84, 90 at the best size; 3-SAT n =
+// 1000, 5000 10.3, 25.6 against 19, 25.7.  Larger sets fill the CUs with small
+// workgroups (4096 replicas of 4-SAT n = 1000, 2000, 9000: 58, 120, 259 against
+// 70, 85, 156 at 64, 128, 512 threads); the tuner chooses those where they are
+// faster, and a size set by hand is kept.
+bool ksat_takes_split(const KsatDev &I, const SweepCall &C, int block_threads) {
+    return I.sp_lg && C.gpw != 2 && block_threads == 1024 && split_lds_of(I, C) <= kLdsBytes;
+}
+
 hipError_t ksat_launch_sweep(const KsatDev &I, const KsatRepDev &R, const SweepCall &C, int block_threads,
                              hipStream_t s) {
     const size_t lds = ksat_sweep_lds_bytes(I.n, C.n_classes, C.stride);
@@ -1146,18 +1162,13 @@ hipError_t ksat_launch_sweep(const KsatDev &I, const KsatRepDev &R, const SweepC
     }();
     if (attr_split != hipSuccess)
         return attr_split;
-    const size_t split =
-        I.sp_lg ? ksat_split_lds_bytes(I.n, I.n_colors, I.sp_chunks, I.sp_lg, C.n_classes * C.stride, I.sp_waves) : 0;
     if (C.gpw == 2)
         hipLaunchKernelGGL(ksat_sweep_kernel<2>, dim3((R.n_groups + 1) / 2), dim3(block_threads), lds, s, I, R, C);
-    // (also with more groups than CUs: 4096 replicas of n = 200, 1000, 5000, 9000
-    // take 19, 56, 191, 255 us per sweep against 132, 304, 416, 420; a set tuned
-    // to smaller workgroups keeps them)
-    else if (split && split <= kLdsBytes && block_threads == 1024)
+    else if (ksat_takes_split(I, C, block_threads))
         hipLaunchKernelGGL(I.sp_lg == 2   ? ksat_split_kernel<2>
                            : I.sp_lg == 3 ? ksat_split_kernel<3>
                                           : ksat_split_kernel<4>,
-                           dim3(R.n_groups), dim3(64 * I.sp_waves), split, s, I, R, C);
+                           dim3(R.n_groups), dim3(64 * I.sp_waves), split_lds_of(I, C), s, I, R, C);
     else
         hipLaunchKernelGGL(ksat_sweep_kernel<1>, dim3(R.n_groups), dim3(block_threads), lds, s, I, R, C);
     return hipGetLastError();
