@@ -574,7 +574,9 @@ int nmc_batch_set_tuning(nmc_batch *batch, int32_t block_threads);
  * classes by work (N x R), and each class in turn takes 8 when that makes the
  * batched probe at least 1 % faster (each configuration is timed twice and
  * the shorter time counts).  Each set keeps its choice for later
- * calls.  Results never depend on the tuning. */
+ * batched calls, and for single calls unless those run several lanes per
+ * variable (instances of small colour classes at the default workgroup size),
+ * which the probe does not time.  Results never depend on the tuning. */
 int nmc_batch_tune(nmc_batch *batch, int32_t probe_sweeps, int32_t *chosen, void *stream);
 
 /* nmc_anneal for every set of the batch in one launch per kernel kind: one

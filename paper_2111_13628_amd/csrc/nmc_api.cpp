@@ -1139,6 +1139,7 @@ struct nmc_replicas {
     bool has_backbone = false;
     int32_t block_threads = 1024;
     int32_t gpw = 1;  // k-SAT sweep: groups of 4 replicas per workgroup (1 or 2)
+    bool gpw_batch = false;  // gpw is a batch tuner's choice
     // library-owned threshold / class upload buffer
     uint8_t *tab_dev = nullptr;
     size_t tab_cap = 0;
@@ -1515,7 +1516,9 @@ static int anneal_impl(nmc_replicas *P, const double *beta, int32_t n_classes, i
         C.check_start = 1;
         C.key0 = (uint32_t)P->seed;
         C.key1 = (uint32_t)(P->seed >> 32);
-        C.gpw = P->gpw;
+        // (a batch tuner compares general sweeps only, and says nothing about
+        // the split ones)
+        C.gpw = P->gpw_batch && ksat_takes_split(I->ksat_dev(), C, P->block_threads) ? 1 : P->gpw;
         if (I->wide) {
             // variable-major spins for the call's sweeps, back to the
             // group-major state afterwards
@@ -1834,6 +1837,7 @@ int nmc_set_replicas_per_workgroup(nmc_replicas *P, int32_t reps) {
     if (reps != kGroup && reps != 2 * kGroup)
         return fail(NMC_ERR_INVALID, "replicas per workgroup must be 4 or 8");
     P->gpw = reps / kGroup;
+    P->gpw_batch = false;
     return ok();
 }
 
@@ -3959,8 +3963,10 @@ extern "C" int nmc_batch_tune(nmc_batch *B, int32_t probe_sweeps, int32_t *chose
             return rc;
         guard.keep = true;
         B->block_threads = best_b;
-        for (size_t i = 0; i < ks.size(); ++i)
+        for (size_t i = 0; i < ks.size(); ++i) {
             ks[i]->gpw = gsel[i];
+            ks[i]->gpw_batch = true;
+        }
         if (chosen)
             *chosen = best_b;
         return ok();
@@ -4008,6 +4014,7 @@ extern "C" int nmc_tune(nmc_replicas *P, int32_t probe_sweeps, int32_t *block_th
         guard.clone = rebased(P, guard.scratch);
         nmc_replicas &C = guard.clone;
         C.profiling = true;
+        C.gpw_batch = false;
         const std::vector<double> beta((size_t)probe_sweeps, 1.0);
         // kernel time of probe_sweeps sweeps by the launch that the set would
         // make (the shorter of two; the copy's states move on)
@@ -4055,6 +4062,7 @@ extern "C" int nmc_tune(nmc_replicas *P, int32_t probe_sweeps, int32_t *block_th
         }
         P->block_threads = best_b;
         P->gpw = best_g;
+        P->gpw_batch = false;
         if (block_threads)
             *block_threads = P->block_threads;
         if (reps_per_workgroup)

@@ -426,3 +426,16 @@ def test_tuned_set_is_not_slower(n, k, alpha, R):
     ta, tb = sweep_ms(a), sweep_ms(b)
     assert (a.get_state() == b.get_state()).all()
     assert tb < 1.25 * ta, (block, reps, ta, tb)
+
+
+def test_batch_tuner_leaves_single_calls():
+    """8 replicas per workgroup chosen for a batched launch do not take a
+    member's own calls off the split sweeps."""
+    say("case: single calls of batch-tuned sets")
+    cp, lits = instances.gen_ksat(2000, "9.8", 4, 5)
+    inst = nmc.Instance.ksat(2000, cp, lits).bind()
+    sets = [nmc.Replicas(inst, 4096, 9 + i) for i in range(16)]
+    untuned = sweep_ms(nmc.Replicas(inst, 4096, 9))
+    nmc.Batch(sets).tune(3)
+    say(f"replicas per workgroup: {[s.replicas_per_workgroup() for s in sets]}")
+    assert max(sweep_ms(s) for s in sets[::3]) < 1.25 * untuned
