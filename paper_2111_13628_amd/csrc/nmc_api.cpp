@@ -1518,7 +1518,7 @@ static int anneal_impl(nmc_replicas *P, const double *beta, int32_t n_classes, i
         C.key1 = (uint32_t)(P->seed >> 32);
         // (a batch tuner compares general sweeps only, and says nothing about
         // the split ones)
-        C.gpw = P->gpw_batch && ksat_takes_split(I->ksat_dev(), C, P->block_threads) ? 1 : P->gpw;
+        C.gpw = P->gpw_batch && ksat_takes_split(I->ksat_dev(), P->G, C, P->block_threads) ? 1 : P->gpw;
         if (I->wide) {
             // variable-major spins for the call's sweeps, back to the
             // group-major state afterwards
@@ -4032,13 +4032,16 @@ extern "C" int nmc_tune(nmc_replicas *P, int32_t probe_sweeps, int32_t *block_th
         };
         // the workgroup size with 4 replicas per workgroup (1024: the split
         // sweeps where the set has them), then 8 at the best general size
-        int best_b = 0, general_b = 0, best_g = 1;
-        double best_ms = 0, general_ms = 0;
+        int best_b = 0, general_b = 1024, best_g = 1;
+        double best_ms = 0, general_ms = INFINITY;
         SweepCall probe{};
         probe.n_classes = 1;
         probe.stride = P->inst->dmax + 1;
         probe.gpw = 1;
-        for (int cand : {64, 128, 256, 512, 1024}) {
+        for (int cand : {1024, 512, 256, 128, 64}) {
+            const bool split = ksat_takes_split(P->inst->ksat_dev(), P->G, probe, cand);
+            if (split && cand != 1024)
+                continue;  // (the same launch)
             double ms = 0;
             if (int rc = time_config(cand, 1, &ms))
                 return rc;
@@ -4046,7 +4049,7 @@ extern "C" int nmc_tune(nmc_replicas *P, int32_t probe_sweeps, int32_t *block_th
                 best_b = cand;
                 best_ms = ms;
             }
-            if (!ksat_takes_split(P->inst->ksat_dev(), probe, cand) && (general_b == 0 || ms < general_ms)) {
+            if (!split && ms < general_ms) {
                 general_b = cand;
                 general_ms = ms;
             }

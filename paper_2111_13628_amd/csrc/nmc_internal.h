@@ -265,7 +265,7 @@ hipError_t ksat_launch_recount(const KsatDev &I, const uint8_t *xs, int n_groups
                                hipStream_t s);
 hipError_t ksat_launch_reset_tallies(const KsatRepDev &R, int n, hipStream_t s);
 // whether ksat_launch_sweep runs the call as split sweeps
-bool ksat_takes_split(const KsatDev &I, const SweepCall &C, int block_threads);
+bool ksat_takes_split(const KsatDev &I, int n_groups, const SweepCall &C, int block_threads);
 hipError_t ksat_launch_sweep(const KsatDev &I, const KsatRepDev &R, const SweepCall &C, int block_threads,
                              hipStream_t s);
 hipError_t ksat_launch_backbone(const KsatDev &I, const KsatRepDev &R, int thr_num, int thr_den, int expand,

@@ -1133,9 +1133,13 @@ static size_t split_lds_of(const KsatDev &I, const SweepCall &C) {
 // 1000, 5000 10.3, 25.6 against 19, 25.7.  Larger sets fill the CUs with small
 // workgroups (4096 replicas of 4-SAT n = 1000, 2000, 9000: 58, 120, 259 against
 // 70, 85, 156 at 64, 128, 512 threads); the tuner chooses those where they are
-// faster, and a size set by hand is kept.
-bool ksat_takes_split(const KsatDev &I, const SweepCall &C, int block_threads) {
-    return I.sp_lg && C.gpw != 2 && block_threads == 1024 && split_lds_of(I, C) <= kLdsBytes;
+// faster, and a size set by hand is kept, but for the smallest instances: with
+// kSplitAnySize clauses or fewer and up to 4096 replicas a general sweep takes
+// 1.6 to 2.2 times as long at every size (4-SAT n = 60: 28 against 14 us).
+bool ksat_takes_split(const KsatDev &I, int n_groups, const SweepCall &C, int block_threads) {
+    constexpr int kSplitAnySize = 2048;
+    const bool sized = block_threads == 1024 || (I.m <= kSplitAnySize && n_groups <= 1024);
+    return I.sp_lg && C.gpw != 2 && sized && split_lds_of(I, C) <= kLdsBytes;
 }
 
 hipError_t ksat_launch_sweep(const KsatDev &I, const KsatRepDev &R, const SweepCall &C, int block_threads,
@@ -1164,7 +1168,7 @@ hipError_t ksat_launch_sweep(const KsatDev &I, const KsatRepDev &R, const SweepC
         return attr_split;
     if (C.gpw == 2)
         hipLaunchKernelGGL(ksat_sweep_kernel<2>, dim3((R.n_groups + 1) / 2), dim3(block_threads), lds, s, I, R, C);
-    else if (ksat_takes_split(I, C, block_threads))
+    else if (ksat_takes_split(I, R.n_groups, C, block_threads))
         hipLaunchKernelGGL(I.sp_lg == 2   ? ksat_split_kernel<2>
                            : I.sp_lg == 3 ? ksat_split_kernel<3>
                                           : ksat_split_kernel<4>,

@@ -439,3 +439,17 @@ def test_batch_tuner_leaves_single_calls():
     nmc.Batch(sets).tune(3)
     say(f"replicas per workgroup: {[s.replicas_per_workgroup() for s in sets]}")
     assert max(sweep_ms(s) for s in sets[::3]) < 1.25 * untuned
+
+
+@pytest.mark.parametrize("n,k,alpha,threads", [(60, 4, "9.8", 64), (200, 4, "9.6", 512), (200, 3, "4.15", 256)])
+def test_small_instance_at_any_workgroup_size(n, k, alpha, threads):
+    """The smallest instances run the same sweeps at every workgroup size: one set
+    by hand does not slow them (general sweeps take twice as long)."""
+    say(f"case: small n={n} k={k} threads={threads}")
+    cp, lits = instances.gen_ksat(n, alpha, k, n)
+    inst = nmc.Instance.ksat(n, cp, lits).bind()
+    a, b = nmc.Replicas(inst, 64, 7), nmc.Replicas(inst, 64, 7)
+    b.set_tuning(threads)
+    ta, tb = sweep_ms(a), sweep_ms(b)
+    assert (a.get_state() == b.get_state()).all()
+    assert tb < 1.25 * ta, (ta, tb)
