@@ -21,6 +21,7 @@
 // equals the sequential colour-major order.  The instance (per-variable
 // clause records) streams from L2/MALL, shared by every workgroup.
 #include <climits>
+#include <cstdlib>
 #include <type_traits>
 
 #include "nmc_internal.h"
@@ -1136,10 +1137,15 @@ static size_t split_lds_of(const KsatDev &I, const SweepCall &C) {
 // faster, and a size set by hand is kept, but for the smallest instances: with
 // kSplitAnySize clauses or fewer and up to 4096 replicas a general sweep takes
 // 1.6 to 2.2 times as long at every size (4-SAT n = 60: 28 against 14 us).
+// NMC_KSAT_STAGE=0, read at every launch, keeps the general sweeps, so that a
+// process can compare the two.
 bool ksat_takes_split(const KsatDev &I, int n_groups, const SweepCall &C, int block_threads) {
     constexpr int kSplitAnySize = 2048;
     const bool sized = block_threads == 1024 || (I.m <= kSplitAnySize && n_groups <= 1024);
-    return I.sp_lg && C.gpw != 2 && sized && split_lds_of(I, C) <= kLdsBytes;
+    if (!I.sp_lg || C.gpw == 2 || !sized || split_lds_of(I, C) > kLdsBytes)
+        return false;
+    const char *e = std::getenv("NMC_KSAT_STAGE");
+    return !(e && e[0] == '0');
 }
 
 hipError_t ksat_launch_sweep(const KsatDev &I, const KsatRepDev &R, const SweepCall &C, int block_threads,

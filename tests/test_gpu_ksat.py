@@ -453,3 +453,17 @@ def test_small_instance_at_any_workgroup_size(n, k, alpha, threads):
     ta, tb = sweep_ms(a), sweep_ms(b)
     assert (a.get_state() == b.get_state()).all()
     assert tb < 1.25 * ta, (ta, tb)
+
+
+def test_general_sweeps_on_request(monkeypatch):
+    """NMC_KSAT_STAGE=0 keeps an instance on the general sweeps (read at every
+    launch; they take twice as long here), with the same results."""
+    say("case: general sweeps on request n=200")
+    cp, lits = instances.gen_ksat(200, "9.6", 4, SEED)
+    inst = nmc.Instance.ksat(200, cp, lits).bind()
+    a, b = nmc.Replicas(inst, 64, 7), nmc.Replicas(inst, 64, 7)
+    ta = sweep_ms(a)
+    monkeypatch.setenv("NMC_KSAT_STAGE", "0")
+    tb = sweep_ms(b)
+    assert (a.get_state() == b.get_state()).all()
+    assert tb > 1.4 * ta, (ta, tb)
