@@ -291,6 +291,10 @@ void run_workers(size_t threads, F fn) {
         std::rethrow_exception(error);
 }
 
+// Records (a clause once for each of its variables) per thread that loads an
+// instance: some 0.6 ms of placement.
+constexpr size_t kLoadThreadRecords = 2500;
+
 size_t host_threads() { return std::max(1u, std::thread::hardware_concurrency()); }
 
 // fn(lo, hi) over [0, n) by host threads, each with 512 KB of work or more
@@ -349,7 +353,8 @@ struct ChunkRec {
     uint32_t neg;
 };
 
-// The 8-byte record of the sweeps: three addresses, then the sign.
+// The 8-byte record of the split sweeps and the whitening passes: three
+// addresses, then the sign.
 uint64_t pack_rec(const ChunkRec &r) {
     return (uint64_t)r.a[0] | ((uint64_t)r.a[1] << kAddrBits) | ((uint64_t)r.a[2] << (2 * kAddrBits)) |
            ((uint64_t)r.neg << (3 * kAddrBits));
@@ -370,30 +375,31 @@ uint64_t pack_rec_pair(ChunkRec r) {
 // share one access, different dwords on one bank serialize.  Cost of a
 // half-wave = the largest number of distinct dwords on one bank.
 struct BankLoad {
-    int32_t dw[32][8];
-    int8_t cnt[32];
-    int8_t mx;
+    uint32_t dw[32][8];
+    uint8_t cnt[32];
+    int32_t mx;
     void clear() {
         std::memset(cnt, 0, sizeof cnt);
         mx = 0;
     }
-    // distinct-dword count of the bank after adding dword d (no change)
-    int after(int32_t d) const {
-        const int b = d & 31;
+    bool has(uint32_t d) const {
+        const uint32_t b = d & 31;
         for (int i = 0; i < cnt[b] && i < 8; ++i)
             if (dw[b][i] == d)
-                return cnt[b];
-        return cnt[b] + 1;
+                return true;
+        return false;
     }
-    void add(int32_t d) {
-        const int b = d & 31;
-        for (int i = 0; i < cnt[b] && i < 8; ++i)
-            if (dw[b][i] == d)
-                return;
+    // cost of one more dword on a bank of c: 64 if the worst bank grows, and
+    // the dwords already there
+    int32_t cost(int32_t c) const { return (c + 1 > mx ? 64 : 0) + c; }
+    void add(uint32_t d) {
+        const uint32_t b = d & 31;
+        if (has(d))
+            return;
         if (cnt[b] < 8)
-            dw[b][(int)cnt[b]] = d;
+            dw[b][cnt[b]] = d;
         cnt[b]++;
-        mx = std::max<int8_t>(mx, cnt[b]);
+        mx = std::max<int32_t>(mx, cnt[b]);
     }
 };
 
@@ -402,67 +408,158 @@ struct BankLoad {
 // bank in each half-wave.  Greedy per slot: lanes take, in turn, the record
 // and address order that raises the half-wave's worst bank least, then loads
 // the fewest-used banks; the most loaded lanes go first.  Any placement gives
-// the same results; only the gathers' bank conflicts change.  With pair16 the
-// first and third addresses of a record agree in bit 16 (see pack_rec_pair).
-void schedule_chunk(std::vector<std::vector<ChunkRec>> &lanes, int32_t nslot, bool optimize,
-                    std::vector<ChunkRec> &out /* [nslot][64] */, const ChunkRec &dummy, bool pair16 = false) {
-    static const int perms[6][3] = {{0, 1, 2}, {1, 2, 0}, {2, 0, 1}, {0, 2, 1}, {1, 0, 2}, {2, 1, 0}};
-    out.assign((size_t)nslot * kChunk, dummy);
-    if (!optimize) {
-        for (int l = 0; l < kChunk; ++l)
-            for (size_t s = 0; s < lanes[l].size(); ++s)
-                out[s * kChunk + l] = lanes[l][s];
-        return;
+// the same results; only the gathers' bank conflicts change.
+//
+// Loading an instance spends most of its time here, so a record's six orders
+// are priced at once: per bank and address of the record, a vector holds what
+// that address costs in each order, kept up to date as dwords are added, and a
+// record's costs are the sum of three of them.  Dwords that a half-wave already
+// reads cost less; a bit per hashed dword finds the few records to correct.
+// (One order and address at a time: N = 50,000 placed in 780 ms of CPU time per
+// layout, now 180.)
+class ChunkPlacer {
+public:
+    std::vector<ChunkRec> out;  // [slots][64 lanes]
+
+    ChunkPlacer(int32_t max_slots, bool optimize, const ChunkRec &dummy)
+        : out((size_t)max_slots * kChunk), rec((size_t)max_slots * kChunk), cap(max_slots), optimize(optimize),
+          dummy(dummy) {
+        for (int p = 0; p < 6; ++p)
+            for (int j = 0; j < 3; ++j)
+                unit[perms[p][j]][j][p] = 1;
+        for (int t = 0; t < 8; ++t)
+            for (int p = 0; p < 6; ++p)
+                refused[t][p] = ((t >> perms[p][0] ^ t >> perms[p][2]) & 1) ? kRefused : 0;
+        for (auto &of_bank : price)
+            of_bank[0][6] = of_bank[0][7] = kRefused;  // (there are six orders)
     }
-    std::vector<int> order(kChunk);
-    BankLoad load[3][2];
-    for (int32_t s = 0; s < nslot; ++s) {
-        for (int j = 0; j < 3; ++j)
-            for (int h = 0; h < 2; ++h)
-                load[j][h].clear();
-        // lanes without records read the inert dummy in this slot
-        for (int l = 0; l < kChunk; ++l)
-            if (lanes[l].empty())
-                for (int j = 0; j < 3; ++j)
-                    load[j][l / 32].add((int32_t)(dummy.a[j] >> 2));
-        std::iota(order.begin(), order.end(), 0);
-        std::stable_sort(order.begin(), order.end(),
-                         [&](int x, int y) { return lanes[x].size() > lanes[y].size(); });
-        for (int l : order) {
-            std::vector<ChunkRec> &rem = lanes[l];
-            if (rem.empty())
-                continue;
-            const int h = l / 32;
-            // cost: 64 per gather whose worst bank grows, plus the distinct
-            // dwords already on the banks this record's addresses join
-            int best_i = 0, best_p = 0, best_c = 1 << 30;
-            for (size_t i = 0; i < rem.size() && best_c > 0; ++i)
-                for (int p = 0; p < 6 && best_c > 0; ++p) {
-                    if (pair16 && (rem[i].a[perms[p][0]] ^ rem[i].a[perms[p][2]]) >> 16)
-                        continue;
-                    int c = 0;
-                    for (int j = 0; j < 3; ++j) {
-                        const int a = load[j][h].after((int32_t)(rem[i].a[perms[p][j]] >> 2));
-                        c += (a > load[j][h].mx ? 64 : 0) + (a - 1);
-                    }
-                    if (c < best_c) {
-                        best_c = c;
-                        best_i = (int)i;
-                        best_p = p;
-                    }
-                }
-            ChunkRec r = rem[best_i];
-            ChunkRec placed = r;
-            for (int j = 0; j < 3; ++j) {
-                placed.a[j] = r.a[perms[best_p][j]];
-                load[j][h].add((int32_t)(placed.a[j] >> 2));
-            }
-            out[(size_t)s * kChunk + l] = placed;
-            rem[best_i] = rem.back();
-            rem.pop_back();
+    void push(int lane, const ChunkRec &r) { rec[(size_t)lane * cap + left[lane]++] = r; }
+    // The records pushed since the last call, into slots [at, at + nslot) of
+    // out (no lane has more than nslot).  With pair16 the first and third
+    // addresses of a record agree in bit 16 (see pack_rec_pair).
+    void place(int32_t at, int32_t nslot, bool pair16) {
+        std::fill_n(out.begin() + (size_t)at * kChunk, (size_t)nslot * kChunk, dummy);
+        if (!optimize) {
+            for (int l = 0; l < kChunk; ++l)
+                for (int32_t s = 0; s < left[l]; ++s)
+                    out[(size_t)(at + s) * kChunk + l] = rec[(size_t)l * cap + s];
+        } else {
+            place_half(0, at, nslot, pair16);
+            place_half(kChunk / 2, at, nslot, pair16);
+        }
+        std::memset(left, 0, sizeof left);
+    }
+
+private:
+    typedef uint16_t u16x8 __attribute__((vector_size(16)));
+    typedef uint64_t u64x2 __attribute__((vector_size(16)));
+    static constexpr int perms[6][3] = {{0, 1, 2}, {1, 2, 0}, {2, 0, 1}, {0, 2, 1}, {1, 0, 2}, {2, 1, 0}};
+    static constexpr uint16_t kRefused = 0x4000;  // (above every cost)
+
+    std::vector<ChunkRec> rec;  // [64 lanes][cap]
+    int32_t cap;
+    bool optimize;
+    ChunkRec dummy;
+    int32_t left[kChunk] = {};
+    // unit[k][j]: 1 in the orders that gather address k in place j
+    u16x8 unit[3][3] = {}, refused[8] = {};
+    // of one half-wave and slot: per bank and address of a record what it costs
+    // in each order, once every place has a dword (before that all cost the
+    // same); the banks with dwords; and bits of the hashed dwords of each place
+    // and of all
+    u16x8 price[32][3] = {};
+    BankLoad load[3];
+    uint32_t banks = 0;
+    uint64_t seen[4][32];
+
+    static uint32_t dword(uint32_t a) { return a >> 2; }
+    bool maybe(int j, uint32_t d) const { return seen[j][d >> 6 & 31] >> (d & 63) & 1; }
+
+    void start_slot() {
+        for (BankLoad &L : load) {
+            L.clear();
+            L.mx = 1;
+        }
+        std::memset(seen, 0, sizeof seen);
+        for (; banks; banks &= banks - 1) {
+            u16x8 *of_bank = price[__builtin_ctz(banks)];
+            of_bank[0] = of_bank[1] = of_bank[2] = u16x8{};
+            of_bank[0][6] = of_bank[0][7] = kRefused;
         }
     }
-}
+
+    void add(int j, uint32_t d) {
+        BankLoad &L = load[j];
+        const uint32_t b = d & 31;
+        const int32_t mx = L.mx, c = L.cnt[b], before = L.cost(c);
+        L.add(d);
+        banks |= 1u << b;
+        seen[j][d >> 6 & 31] |= 1ull << (d & 63);
+        seen[3][d >> 6 & 31] |= 1ull << (d & 63);
+        if (L.cnt[b] == c)
+            return;
+        for (int k = 0; k < 3; ++k)
+            price[b][k] += (uint16_t)(L.cost(c + 1) - before) * unit[k][j];
+        if (L.mx > mx)  // one more dword on a bank as full as the fullest was costs no more
+            for (uint32_t o = 0; o < 32; ++o)
+                if (o != b && L.cnt[o] == mx)
+                    for (int k = 0; k < 3; ++k)
+                        price[o][k] -= 64 * unit[k][j];
+    }
+
+    void place_half(int lane0, int32_t at, int32_t nslot, bool pair16) {
+        // every lane with records places one per slot, so this order holds for
+        // all slots
+        int order[kChunk / 2];
+        std::iota(order, order + kChunk / 2, lane0);
+        std::stable_sort(order, order + kChunk / 2, [&](int x, int y) { return left[x] > left[y]; });
+        for (int32_t s = 0; s < nslot && left[order[0]]; ++s) {
+            start_slot();
+            // lanes without records read the inert dummy in this slot
+            if (!left[order[kChunk / 2 - 1]])
+                for (int j = 0; j < 3; ++j)
+                    add(j, dword(dummy.a[j]));
+            for (int i = 0; i < kChunk / 2 && left[order[i]]; ++i)
+                place_lane(order[i], at + s, pair16);
+        }
+    }
+
+    void place_lane(int l, int32_t slot, bool pair16) {
+        ChunkRec *rem = &rec[(size_t)l * cap];
+        const int32_t n = left[l];
+        int32_t best_i = 0, best_p = 0;
+        uint16_t best = kRefused - 1;
+        for (int32_t i = 0; i < n && best > 0; ++i) {
+            const uint32_t d[3] = {dword(rem[i].a[0]), dword(rem[i].a[1]), dword(rem[i].a[2])};
+            u16x8 c = price[d[0] & 31][0] + price[d[1] & 31][1] + price[d[2] & 31][2];
+            for (int k = 0; k < 3; ++k)
+                if (maybe(3, d[k]))
+                    for (int j = 0; j < 3; ++j)
+                        if (maybe(j, d[k]) && load[j].has(d[k])) {
+                            const int32_t on = load[j].cnt[d[k] & 31];
+                            c -= (uint16_t)(load[j].cost(on) - (on - 1)) * unit[k][j];
+                        }
+            if (pair16)
+                c += refused[(rem[i].a[0] >> 16) | (rem[i].a[1] >> 16) << 1 | (rem[i].a[2] >> 16) << 2];
+            const u64x2 lower = (u64x2)(c < best);
+            if (lower[0] | lower[1])
+                for (int p = 0; p < 6; ++p)
+                    if (c[p] < best) {
+                        best = c[p];
+                        best_i = i;
+                        best_p = p;
+                    }
+        }
+        ChunkRec &r = out[(size_t)slot * kChunk + l];
+        r.neg = rem[best_i].neg;
+        for (int j = 0; j < 3; ++j) {
+            r.a[j] = rem[best_i].a[perms[best_p][j]];
+            add(j, dword(r.a[j]));
+        }
+        rem[best_i] = rem[n - 1];
+        left[l] = n - 1;
+    }
+};
 
 // Modeled LDS cycles of a chunk's gathers (sum over slots, positions and
 // half-waves of the worst bank's distinct dwords).
@@ -474,7 +571,7 @@ int64_t chunk_gather_cycles(const std::vector<ChunkRec> &placed, int32_t nslot) 
             for (int h = 0; h < 2; ++h) {
                 bl.clear();
                 for (int l = h * 32; l < h * 32 + 32; ++l)
-                    bl.add((int32_t)(placed[(size_t)s * kChunk + l].a[j] >> 2));
+                    bl.add(placed[(size_t)s * kChunk + l].a[j] >> 2);
                 cyc += bl.mx;
             }
     return cyc;
@@ -593,179 +690,69 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
         const char *split_env = std::getenv("NMC_KSAT_SPLIT");
         const bool split = !(split_env && split_env[0] == '0');
         const bool debug_banks = std::getenv("NMC_DEBUG_BANKS") != nullptr;
-        int64_t model_cycles = 0, model_gathers = 0;
-        std::vector<int32_t> chunk_var, color_chunk(ncol + 1, 0);
-        std::vector<int2> chunk_info;
-        std::vector<uint64_t> rec;
-        int32_t slot_rows = 0;
-        if (!I->wide) {
-        // (1) every chunk's lanes and records, (2) placement (chunks are
-        // independent: spread over host threads for large instances), (3) the
-        // packed record image in chunk order
-        struct ChunkWork {
-            std::vector<std::vector<ChunkRec>> lanes;
-            int32_t nslot = 0;
-            std::vector<ChunkRec> placed;
+        std::atomic<int64_t> model_cycles{0}, model_gathers{0};
+        auto deg = [&](int32_t v) { return vptr[v + 1] - vptr[v]; };
+        auto even = [](int32_t x) { return (x + 1) / 2 * 2; };
+        // The layouts are planned first (their chunks, variables by degree inside
+        // a class, and sizes), then the records of all chunks are gathered,
+        // placed and written to the image by several threads.
+        std::vector<int32_t> vs = I->order;
+        for (int32_t c = 0; c < ncol; ++c)
+            std::stable_sort(vs.begin() + I->color_ptr[c], vs.begin() + I->color_ptr[c + 1],
+                             [&](int32_t x, int32_t y) { return deg(x) > deg(y); });
+        // whitening: a class's variables in groups of 64.  A chunk of few
+        // variables gives each variable 2^lg adjacent lanes (its clauses dealt
+        // round-robin over them), so a lane walks about 1 / 2^lg of the
+        // variable's slots; the lanes' partial results are joined
+        struct Chunk {
+            int32_t b, e, lg;  // vs[b, e), each on 2^lg lanes
         };
-        std::vector<ChunkWork> work;
-        for (int32_t c = 0; c < ncol; ++c) {
-            std::vector<int32_t> vs(I->order.begin() + I->color_ptr[c], I->order.begin() + I->color_ptr[c + 1]);
-            std::stable_sort(vs.begin(), vs.end(), [&](int32_t x, int32_t y) {
-                return (vptr[x + 1] - vptr[x]) > (vptr[y + 1] - vptr[y]);
-            });
-            for (size_t b = 0; b < vs.size(); b += kChunk) {
-                const size_t e = std::min(vs.size(), b + kChunk);
-                // a chunk of few variables gives each variable L = 2^lg
-                // adjacent lanes (its clauses dealt round-robin over them), so
-                // a lane walks about 1/L of the variable's slots; the lanes'
-                // partial sums are added before the decision
+        std::vector<Chunk> wh, sp;
+        std::vector<int32_t> color_chunk(ncol + 1, 0), sp_color(ncol + 1, 0), bl_color(ncol + 1, 0);
+        std::vector<int2> chunk_info, sp_info;
+        int32_t slot_rows = 0;
+        for (int32_t c = 0; c < ncol && !I->wide; ++c) {
+            for (int32_t b = I->color_ptr[c]; b < I->color_ptr[c + 1]; b += kChunk) {
+                const int32_t e = std::min(I->color_ptr[c + 1], b + kChunk);
                 int32_t lg = 0;
-                while (split && lg < kMaxSplitLog && (int32_t)(e - b) << (lg + 1) <= kChunk)
+                while (split && lg < kMaxSplitLog && (e - b) << (lg + 1) <= kChunk)
                     ++lg;
-                const int32_t L = 1 << lg;
-                int32_t nslot = 0;
-                for (size_t i = b; i < e; ++i)
-                    nslot = std::max(nslot, (vptr[vs[i] + 1] - vptr[vs[i]] + L - 1) / L);
-                nslot = std::max<int32_t>(kSlotUnroll, (int32_t)align_up(nslot, kSlotUnroll));  // padding slots are inert
+                // (descending degrees: the first variable has the most clauses;
+                // padding slots are inert)
+                const int32_t L = 1 << lg, slots = (deg(vs[b]) + L - 1) / L;
+                const int32_t nslot = std::max<int32_t>(kSlotUnroll, (int32_t)align_up(slots, kSlotUnroll));
                 chunk_info.push_back(make_int2(slot_rows, nslot | (lg << kSplitShift)));
                 slot_rows += nslot;
-                ChunkWork w;
-                w.lanes.resize(kChunk);
-                w.nslot = nslot;
-                int32_t n1[kChunk] = {0};
-                for (size_t i = b; i < e; ++i) {
-                    const int lane0 = (int)(i - b) * L;
-                    const int32_t v = vs[i];
-                    for (int32_t q = vptr[v]; q < vptr[v + 1]; ++q) {
-                        const int32_t a = vcl[q], own = vpos[q];
-                        const int lane = lane0 + (q - vptr[v]) % L;
-                        ChunkRec r{{ZERO, ZERO, ZERO}, lits[own] < 0 ? 1u : 0u};
-                        int k = 0;
-                        for (int32_t p = clause_ptr[a]; p < clause_ptr[a + 1]; ++p)
-                            if (p != own)
-                                r.a[k++] = lit_addr(lits[p]);
-                        n1[lane] += (int32_t)r.neg;
-                        w.lanes[lane].push_back(r);
-                    }
-                }
-                work.push_back(std::move(w));
-                // lane word: variable in bits 0..19 and the count of the lane's
-                // records whose own literal is negated in bits 20..27; -1 =
-                // empty lane
-                for (int lane = 0; lane < kChunk; ++lane) {
-                    const size_t i = b + (size_t)(lane / L);
-                    chunk_var.push_back(i < e ? (vs[i] | (n1[lane] << 20)) : -1);
-                }
+                wh.push_back({b, e, lg});
             }
-            color_chunk[c + 1] = (int32_t)chunk_info.size();
+            color_chunk[c + 1] = (int32_t)wh.size();
         }
-        {
-            const ChunkRec dummy{{ONES, ZERO, ZERO}, 0u};
-            std::atomic<size_t> next{0};
-            auto worker = [&] {
-                for (size_t i; (i = next.fetch_add(1)) < work.size();)
-                    schedule_chunk(work[i].lanes, work[i].nslot, bank_schedule, work[i].placed, dummy);
-            };
-            run_workers(bank_schedule && vcl.size() >= 20000 ? host_threads() : 1, worker);
-        }
-        rec.resize((size_t)slot_rows * kChunk);
-        for (size_t i = 0; i < work.size(); ++i) {
-            const int32_t nslot = work[i].nslot;
-            const std::vector<ChunkRec> &placed = work[i].placed;
-            if (debug_banks) {
-                model_cycles += chunk_gather_cycles(placed, nslot);
-                model_gathers += 3 * (int64_t)nslot;
-            }
-            const size_t base = (size_t)chunk_info[i].x * kChunk;
-            // slots are stored in pairs: [slot / 2][lane][slot % 2], so one
-            // 16-byte load gives a lane two consecutive slots
-            for (int32_t sl = 0; sl < nslot; ++sl)
-                for (int lane = 0; lane < kChunk; ++lane) {
-                    const ChunkRec &r = placed[(size_t)sl * kChunk + lane];
-                    rec[base + (size_t)(sl / 2) * 2 * kChunk + (size_t)lane * 2 + (sl & 1)] = pack_rec(r);
-                }
-        }
-        I->n_chunks = (int32_t)chunk_info.size();
-        if (debug_banks && model_gathers)
-            std::fprintf(stderr, "nmc: %d chunks, %lld slot gathers, modeled %.3f LDS cycles per gather\n",
-                         I->n_chunks, (long long)model_gathers, (double)model_cycles / (double)model_gathers);
-        }  // !I->wide
+        I->n_chunks = (int32_t)wh.size();
         // split layout: every class's variables on 2^lg lanes each (lg fixed per
         // instance: a class then fills about four waves, one per SIMD), the
         // clauses dealt round-robin over a variable's lanes
-        std::vector<uint64_t> sp_rec;
-        std::vector<int32_t> sp_color(ncol + 1, 0);
-        std::vector<int2> sp_info, sp_var;
-        int32_t lg = 2, split_chunks = 0, split_waves = 0;
-        while (lg < kMaxSplitLog && ((int64_t)n << (lg + 1)) <= (int64_t)256 * ncol)
-            ++lg;
+        int32_t sp_lg = 2, split_chunks = 0, split_waves = 0, sp_rows = 0;
+        while (sp_lg < kMaxSplitLog && ((int64_t)n << (sp_lg + 1)) <= (int64_t)256 * ncol)
+            ++sp_lg;
         for (int32_t c = 0; c < ncol; ++c) {
-            const int32_t k = ((I->color_ptr[c + 1] - I->color_ptr[c]) + (kChunk >> lg) - 1) / (kChunk >> lg);
+            const int32_t k = ((I->color_ptr[c + 1] - I->color_ptr[c]) + (kChunk >> sp_lg) - 1) / (kChunk >> sp_lg);
             split_chunks += k;
             split_waves = std::max(split_waves, std::min(16, k));
         }
         // (only where a sweep with one threshold row fits in LDS)
         if (!I->wide && split && (int64_t)n <= (int64_t)kSplitMaxClass * ncol &&
-            ksat_split_lds_bytes(n, ncol, split_chunks, lg, dmax + 1, split_waves) <= kLdsBytes) {
-            const int32_t L = 1 << lg, per = kChunk >> lg;
-            struct SplitChunk {
-                std::vector<std::vector<ChunkRec>> lanes;
-                std::vector<ChunkRec> placed;
-            };
-            std::vector<SplitChunk> work;
-            int32_t rows = 0;
+            ksat_split_lds_bytes(n, ncol, split_chunks, sp_lg, dmax + 1, split_waves) <= kLdsBytes) {
+            const int32_t L = 1 << sp_lg, per = kChunk >> sp_lg;
             for (int32_t c = 0; c < ncol; ++c) {
-                std::vector<int32_t> vs(I->order.begin() + I->color_ptr[c], I->order.begin() + I->color_ptr[c + 1]);
-                std::stable_sort(vs.begin(), vs.end(), [&](int32_t x, int32_t y) {
-                    return (vptr[x + 1] - vptr[x]) > (vptr[y + 1] - vptr[y]);
-                });
-                for (size_t b = 0; b < vs.size(); b += per) {
-                    const size_t e = std::min(vs.size(), b + per);
-                    // (descending degrees: the first variable has the most clauses)
-                    const int32_t slots = std::max(1, (vptr[vs[b] + 1] - vptr[vs[b]] + L - 1) / L);
-                    const int32_t pairs = (slots + 1) / 2;
-                    sp_info.push_back(make_int2(rows, pairs));
-                    rows += pairs;
-                    SplitChunk w;
-                    w.lanes.resize(kChunk);
-                    std::vector<int32_t> n1(kChunk, 0);
-                    for (size_t i = b; i < e; ++i) {
-                        const int32_t v = vs[i];
-                        for (int32_t q = vptr[v]; q < vptr[v + 1]; ++q) {
-                            const int32_t a = vcl[q], own = vpos[q], lane = (int32_t)(i - b) * L + (q - vptr[v]) % L;
-                            ChunkRec r{{ZERO, ZERO, ZERO}, lits[own] < 0 ? 1u : 0u};
-                            int k = 0;
-                            for (int32_t p = clause_ptr[a]; p < clause_ptr[a + 1]; ++p)
-                                if (p != own)
-                                    r.a[k++] = lit_addr(lits[p]);
-                            n1[lane] += (int32_t)r.neg;
-                            w.lanes[lane].push_back(r);
-                        }
-                    }
-                    work.push_back(std::move(w));
-                    for (int lane = 0; lane < kChunk; ++lane) {
-                        const size_t i = b + (size_t)(lane >> lg);
-                        const uint32_t kk = (uint32_t)(2 * pairs - 2 * n1[lane]) * 0x01010101u - (uint32_t)n1[lane] +
-                                            (lane % L ? 0u : 0x80808080u);
-                        sp_var.push_back(make_int2(i < e ? vs[i] : -1, (int32_t)kk));
-                    }
+                for (int32_t b = I->color_ptr[c]; b < I->color_ptr[c + 1]; b += per) {
+                    const int32_t pairs = (std::max(1, (deg(vs[b]) + L - 1) / L) + 1) / 2;
+                    sp_info.push_back(make_int2(sp_rows, pairs));
+                    sp_rows += pairs;
+                    sp.push_back({b, std::min(I->color_ptr[c + 1], b + per), sp_lg});
                 }
-                sp_color[c + 1] = (int32_t)sp_info.size();
+                sp_color[c + 1] = (int32_t)sp.size();
             }
-            const ChunkRec dummy{{ONES, ZERO, ZERO}, 0u};
-            std::atomic<size_t> next{0};
-            auto worker = [&] {
-                for (size_t i; (i = next.fetch_add(1)) < work.size();)
-                    schedule_chunk(work[i].lanes, 2 * sp_info[i].y, bank_schedule, work[i].placed, dummy);
-            };
-            run_workers(bank_schedule && vcl.size() >= 20000 ? host_threads() : 1, worker);
-            sp_rec.resize((size_t)(rows + kSplitAhead) * kChunk * 2);  // (the last chunk's reads ahead end in zeros)
-            for (size_t i = 0; i < work.size(); ++i)
-                for (int32_t sl = 0; sl < 2 * sp_info[i].y; ++sl)
-                    for (int lane = 0; lane < kChunk; ++lane)
-                        sp_rec[(size_t)(sp_info[i].x + sl / 2) * 2 * kChunk + (size_t)lane * 2 + (sl & 1)] =
-                            pack_rec(work[i].placed[(size_t)sl * kChunk + lane]);
-            I->sp_lg = lg;
+            I->sp_lg = sp_lg;
             I->sp_chunks = split_chunks;
             I->sp_waves = split_waves;
         }
@@ -775,138 +762,56 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
         // them or fewer, its variables (those of middle degree) take 2^lg lanes
         // each.  (With a single round that would multiply the decisions of the
         // batched sweeps, which run such classes on fewer waves: there only a
-        // last chunk of few variables is spread, over its own lanes.)  All others go in pairs of a heavy variable (even lane) and a
-        // light one (odd lane): the light lane walks `ws` slots of its own, then
-        // the heavy one's remaining clauses.
-        std::vector<uint32_t> bl_rec;
-        std::vector<int32_t> bl_var, bl_color(ncol + 1, 0);
+        // last chunk of few variables is spread, over its own lanes.)  All others
+        // go in pairs of a heavy variable (even lane) and a light one (odd lane):
+        // the light lane walks `ws` slots of its own, then the heavy one's
+        // remaining clauses.
+        struct SweepChunk {
+            int32_t c0, first, nv, P;  // the class's variables from vs[c0]; paired: all but [first, first + nv)
+            int32_t b, e;              // pairs [b, e), or with lg > 0 variables c0 + [b, e)
+        };
+        std::vector<SweepChunk> bl;
         std::vector<int4> bl_info;
-        if (!I->wide) {
-            // a chunk is placed in two parts: slots below ws, slots from ws on
-            struct SweepChunk {
-                std::vector<std::vector<ChunkRec>> lanes[2];
-                std::vector<ChunkRec> placed[2];
-            };
-            std::vector<SweepChunk> work;
-            // a variable alone in its chunk has 66 slots at most, and 64 share
-            // 128: byte offsets stay below 2^32, and not below 2^31
-            constexpr uint64_t most = 9 * kBlockSign + 33 * kBlockRow;
-            static_assert(2 * most >= 16 * kBlockSign + 64 * kBlockRow && kMaxVars * most + kBlockBytes <= UINT32_MAX);
-            uint32_t bytes = 0;
-            auto deg = [&](int32_t v) { return vptr[v + 1] - vptr[v]; };
-            auto even = [](int32_t x) { return (x + 1) / 2 * 2; };
-            auto rec_of = [&](int32_t q) {
-                const int32_t a = vcl[q], own = vpos[q];
-                ChunkRec r{{ZERO, ZERO, ZERO}, lits[own] < 0 ? 1u : 0u};
-                int k = 0;
-                for (int32_t p = clause_ptr[a]; p < clause_ptr[a + 1]; ++p)
-                    if (p != own)
-                        r.a[k++] = lit_addr(lits[p]);
-                return r;
-            };
-            // lane word of variable v with `slots` slots (padding among them)
-            auto lane_word = [&](int32_t v, int32_t slots) {
-                int32_t neg = 0;
-                for (int32_t q = vptr[v]; q < vptr[v + 1]; ++q)
-                    neg += lits[vpos[q]] < 0;
-                return v | (int32_t)((uint32_t)(slots - neg) << 20);
-            };
-            auto add_chunk = [&](SweepChunk &&w, int32_t nslot, int32_t lg, int32_t ws) {
-                bl_info.push_back(make_int4((int32_t)bytes, nslot, lg, ws));
-                bytes += (uint32_t)((nslot + 7) / 8 * kBlockSign + nslot / 2 * kBlockRow);
-                work.push_back(std::move(w));
-            };
-            for (int32_t c = 0; c < ncol; ++c) {
-                std::vector<int32_t> vs(I->order.begin() + I->color_ptr[c], I->order.begin() + I->color_ptr[c + 1]);
-                std::stable_sort(vs.begin(), vs.end(), [&](int32_t x, int32_t y) { return deg(x) > deg(y); });
-                const int32_t V = (int32_t)vs.size(), K = (V + kChunk - 1) / kChunk, rem = K % kLayoutWaves;
-                int32_t lg = 0, nv = 0;  // variables on 2^lg lanes: vs[first, first + nv)
-                if (K > kLayoutWaves) {
-                    while (split && rem > 0 && lg < kMaxSplitLog && rem << (lg + 1) <= kLayoutWaves)
-                        ++lg;
-                    nv = lg ? V - (K - rem) * kChunk : 0;
-                } else {
-                    while (split && lg < kMaxSplitLog && V % kChunk << (lg + 1) <= kChunk)
-                        ++lg;
-                    nv = lg ? V % kChunk : 0;
-                }
-                const int32_t first = (V - nv) / 2;
-                const int32_t L = 1 << lg, per = kChunk >> lg;
-                std::vector<int32_t> ps(vs.begin(), vs.begin() + first);
-                ps.insert(ps.end(), vs.begin() + first + nv, vs.end());
-                const int32_t P = (int32_t)ps.size(), pairs = (P + 1) / 2;
-                for (int32_t b = 0; b < pairs; b += kChunk / 2) {
-                    const int32_t e = std::min(pairs, b + kChunk / 2);
-                    int32_t ws = 2, nslot = 2;
-                    for (int32_t i = b; i < e; ++i)
-                        if (P - 1 - i > i)
-                            ws = std::max(ws, even(deg(ps[P - 1 - i])));
-                    for (int32_t i = b; i < e; ++i)
-                        nslot = std::max(nslot, std::max(ws, even((deg(ps[i]) + ws + 1) / 2)));
-                    SweepChunk w;
-                    w.lanes[0].resize(kChunk);
-                    w.lanes[1].resize(kChunk);
-                    std::vector<int32_t> lw(kChunk, -1);
-                    for (int32_t i = b; i < e; ++i) {
-                        const int32_t l = 2 * (i - b), hv = ps[i], d = deg(hv);
-                        for (int32_t k = 0; k < d; ++k)
-                            (k < ws ? w.lanes[0][l] : k < nslot ? w.lanes[1][l] : w.lanes[1][l + 1])
-                                .push_back(rec_of(vptr[hv] + k));
-                        lw[l] = lane_word(hv, 2 * nslot - ws);
-                        if (P - 1 - i > i) {
-                            const int32_t v = ps[P - 1 - i];
-                            for (int32_t q = vptr[v]; q < vptr[v + 1]; ++q)
-                                w.lanes[0][l + 1].push_back(rec_of(q));
-                            lw[l + 1] = lane_word(v, ws);
-                        }
-                    }
-                    bl_var.insert(bl_var.end(), lw.begin(), lw.end());
-                    add_chunk(std::move(w), nslot, 0, ws);
-                }
-                for (int32_t b = first; b < first + nv; b += per) {
-                    const int32_t e = std::min(first + nv, b + per);
-                    // (descending degrees: the first variable has the most clauses)
-                    const int32_t nslot = std::max(2, even((deg(vs[b]) + L - 1) / L));
-                    SweepChunk w;
-                    w.lanes[0].resize(kChunk);
-                    w.lanes[1].resize(kChunk);
-                    std::vector<int32_t> lw(kChunk, -1);
-                    for (int32_t i = b; i < e; ++i) {
-                        const int32_t l = (i - b) * L;
-                        for (int32_t k = 0; k < deg(vs[i]); ++k)
-                            w.lanes[0][l + k % L].push_back(rec_of(vptr[vs[i]] + k));
-                        lw[l] = lane_word(vs[i], L * nslot);
-                    }
-                    bl_var.insert(bl_var.end(), lw.begin(), lw.end());
-                    add_chunk(std::move(w), nslot, lg, nslot);
-                }
-                bl_color[c + 1] = (int32_t)bl_info.size();
+        // a variable alone in its chunk has 66 slots at most, and 64 share 128:
+        // byte offsets stay below 2^32, and not below 2^31
+        constexpr uint64_t most = 9 * kBlockSign + 33 * kBlockRow;
+        static_assert(2 * most >= 16 * kBlockSign + 64 * kBlockRow && kMaxVars * most + kBlockBytes <= UINT32_MAX);
+        uint32_t bl_bytes = 0;
+        auto paired = [&](const SweepChunk &w, int32_t i) { return vs[w.c0 + (i < w.first ? i : i + w.nv)]; };
+        for (int32_t c = 0; c < ncol && !I->wide; ++c) {
+            const int32_t c0 = I->color_ptr[c], V = I->color_ptr[c + 1] - c0;
+            const int32_t K = (V + kChunk - 1) / kChunk, rem = K % kLayoutWaves;
+            int32_t lg = 0, nv = 0;  // variables on 2^lg lanes: c0 + [first, first + nv)
+            if (K > kLayoutWaves) {
+                while (split && rem > 0 && lg < kMaxSplitLog && rem << (lg + 1) <= kLayoutWaves)
+                    ++lg;
+                nv = lg ? V - (K - rem) * kChunk : 0;
+            } else {
+                while (split && lg < kMaxSplitLog && V % kChunk << (lg + 1) <= kChunk)
+                    ++lg;
+                nv = lg ? V % kChunk : 0;
             }
-            const ChunkRec dummy{{ONES, ZERO, ZERO}, 0u};
-            std::atomic<size_t> next{0};
-            bl_rec.resize(((size_t)bytes + kBlockBytes) / 4);  // (a short last block is read whole)
-            auto worker = [&] {
-                for (size_t i; (i = next.fetch_add(1)) < work.size();) {
-                    const int4 f = bl_info[i];
-                    const int32_t nslot = f.y, ws = f.w;
-                    schedule_chunk(work[i].lanes[0], ws, bank_schedule, work[i].placed[0], dummy, true);
-                    schedule_chunk(work[i].lanes[1], nslot - ws, bank_schedule, work[i].placed[1], dummy, true);
-                    for (int32_t sl = 0; sl < nslot; ++sl) {
-                        uint32_t *block = bl_rec.data() + ((uint32_t)f.x + (uint32_t)(sl / 8 * kBlockBytes)) / 4;
-                        const int last = std::min(nslot, (sl / 8 + 1) * 8) - 1;
-                        for (int lane = 0; lane < kChunk; ++lane) {
-                            const ChunkRec &r = sl < ws ? work[i].placed[0][(size_t)sl * kChunk + lane]
-                                                        : work[i].placed[1][(size_t)(sl - ws) * kChunk + lane];
-                            if (r.neg)
-                                block[lane] |= 0xFu << (4 * (last - sl));
-                            const uint64_t w = pack_rec_pair(r);
-                            std::memcpy(block + (kBlockSign + sl % 8 / 2 * kBlockRow) / 4 + lane * 4 + sl % 2 * 2, &w, 8);
-                        }
-                    }
-                    work[i] = SweepChunk();
-                }
+            const int32_t first = (V - nv) / 2, P = V - nv, pairs = (P + 1) / 2, L = 1 << lg, per = kChunk >> lg;
+            auto add_chunk = [&](const SweepChunk &w, int32_t nslot, int32_t lg, int32_t ws) {
+                bl_info.push_back(make_int4((int32_t)bl_bytes, nslot, lg, ws));
+                bl_bytes += (uint32_t)((nslot + 7) / 8 * kBlockSign + nslot / 2 * kBlockRow);
+                bl.push_back(w);
             };
-            run_workers(bank_schedule && vcl.size() >= 20000 ? host_threads() : 1, worker);
+            for (int32_t b = 0; b < pairs; b += kChunk / 2) {
+                const SweepChunk w{c0, first, nv, P, b, std::min(pairs, b + kChunk / 2)};
+                int32_t ws = 2, nslot = 2;
+                for (int32_t i = b; i < w.e; ++i)
+                    if (P - 1 - i > i)
+                        ws = std::max(ws, even(deg(paired(w, P - 1 - i))));
+                for (int32_t i = b; i < w.e; ++i)
+                    nslot = std::max(nslot, std::max(ws, even((deg(paired(w, i)) + ws + 1) / 2)));
+                add_chunk(w, nslot, 0, ws);
+            }
+            for (int32_t b = first; b < first + nv; b += per) {
+                const int32_t nslot = std::max(2, even((deg(vs[c0 + b]) + L - 1) / L));
+                add_chunk({c0, first, nv, P, b, std::min(first + nv, b + per)}, nslot, lg, nslot);
+            }
+            bl_color[c + 1] = (int32_t)bl.size();
         }
         // wide layout: per incidence (var_ptr order) the clause's other
         // literals as spin-table rows (v for x_v, n + 1 + v for NOT x_v, row
@@ -961,8 +866,8 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
         }
 
         Arena ar;
-        I->off_rec = ar.take(rec.size() * 8);
-        I->off_chunk_var = ar.take(chunk_var.size() * 4);
+        I->off_rec = ar.take((size_t)slot_rows * kChunk * 8);
+        I->off_chunk_var = ar.take(wh.size() * kChunk * 4);
         I->off_chunk_info = ar.take(chunk_info.size() * 8);
         I->off_color_chunk = ar.take(color_chunk.size() * 4);
         I->off_clause_addr = ar.take(std::max<size_t>(clause_addr.size() * 4, 16));
@@ -973,16 +878,17 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
             I->off_lbp_pos = ar.take(std::max<size_t>(I->lbp_pos.size() * 4, 4));
         }
         if (I->sp_lg) {
-            I->off_sp_rec = ar.take(sp_rec.size() * 8);
-            I->sp_rec_bytes = (uint32_t)(sp_rec.size() * 8);
-            I->off_sp_var = ar.take(sp_var.size() * 8);
+            // (the last chunk's reads ahead end in zeros)
+            I->sp_rec_bytes = (uint32_t)((size_t)(sp_rows + kSplitAhead) * kChunk * 16);
+            I->off_sp_rec = ar.take(I->sp_rec_bytes);
+            I->off_sp_var = ar.take(sp.size() * kChunk * 8);
             I->off_sp_info = ar.take(sp_info.size() * 8);
             I->off_sp_color = ar.take(sp_color.size() * 4);
         }
         if (!I->wide) {
-            I->off_bl_rec = ar.take(bl_rec.size() * 4);
-            I->bl_rec_bytes = (uint32_t)(bl_rec.size() * 4);
-            I->off_bl_var = ar.take(bl_var.size() * 4);
+            I->bl_rec_bytes = bl_bytes + kBlockBytes;  // (a short last block is read whole)
+            I->off_bl_rec = ar.take(I->bl_rec_bytes);
+            I->off_bl_var = ar.take(bl.size() * kChunk * 4);
             I->off_bl_info = ar.take(bl_info.size() * 16);
             I->off_bl_color = ar.take(bl_color.size() * 4);
         }
@@ -997,8 +903,6 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
             if (bytes)
                 std::memcpy(I->image.data() + off, src, bytes);
         };
-        put(I->off_rec, rec.data(), rec.size() * 8);
-        put(I->off_chunk_var, chunk_var.data(), chunk_var.size() * 4);
         put(I->off_chunk_info, chunk_info.data(), chunk_info.size() * 8);
         put(I->off_color_chunk, color_chunk.data(), color_chunk.size() * 4);
         put(I->off_clause_addr, clause_addr.data(), clause_addr.size() * 4);
@@ -1007,23 +911,162 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
         if (!I->wide) {
             put(I->off_lbp_caddr, lbp_caddr.data(), lbp_caddr.size() * 4);
             put(I->off_lbp_pos, I->lbp_pos.data(), I->lbp_pos.size() * 4);
-        }
-        if (I->sp_lg) {
-            put(I->off_sp_rec, sp_rec.data(), sp_rec.size() * 8);
-            put(I->off_sp_var, sp_var.data(), sp_var.size() * 8);
-            put(I->off_sp_info, sp_info.data(), sp_info.size() * 8);
-            put(I->off_sp_color, sp_color.data(), sp_color.size() * 4);
-        }
-        if (!I->wide) {
-            put(I->off_bl_rec, bl_rec.data(), bl_rec.size() * 4);
-            put(I->off_bl_var, bl_var.data(), bl_var.size() * 4);
             put(I->off_bl_info, bl_info.data(), bl_info.size() * 16);
             put(I->off_bl_color, bl_color.data(), bl_color.size() * 4);
+        }
+        if (I->sp_lg) {
+            put(I->off_sp_info, sp_info.data(), sp_info.size() * 8);
+            put(I->off_sp_color, sp_color.data(), sp_color.size() * 4);
         }
         if (I->wide) {
             put(I->off_wrec, wrec.data(), wrec.size() * sizeof(uint4));
             put(I->off_worder, I->order.data(), (size_t)n * 4);
             put(I->off_wclass, I->color_ptr.data(), I->color_ptr.size() * 4);
+        } else {
+            // the records of every incidence, then every chunk of the layouts
+            std::vector<ChunkRec> recs(vcl.size());
+            const size_t threads = std::min(host_threads(), vcl.size() / kLoadThreadRecords);
+            std::atomic<int32_t> next_var{0};
+            run_workers(threads, [&] {
+                for (int32_t v0; (v0 = next_var.fetch_add(1024)) < n;)
+                    for (int32_t q = vptr[v0]; q < vptr[std::min(n, v0 + 1024)]; ++q) {
+                        const int32_t a = vcl[q], own = vpos[q];
+                        ChunkRec r{{ZERO, ZERO, ZERO}, lits[own] < 0 ? 1u : 0u};
+                        int k = 0;
+                        for (int32_t p = clause_ptr[a]; p < clause_ptr[a + 1]; ++p)
+                            if (p != own)
+                                r.a[k++] = lit_addr(lits[p]);
+                        recs[q] = r;
+                    }
+            });
+            const ChunkRec dummy{{ONES, ZERO, ZERO}, 0u};
+            uint8_t *img = I->image.data();
+            // lane word: variable in bits 0..19 and the count of the lane's
+            // records whose own literal is negated in bits 20..27; -1 = empty
+            // lane.  Slots are stored in pairs: [slot / 2][lane][slot % 2], so
+            // one 16-byte load gives a lane two consecutive slots
+            auto whiten_chunk = [&](size_t i, ChunkPlacer &P) {
+                const Chunk &w = wh[i];
+                const int32_t L = 1 << w.lg, nslot = chunk_info[i].y & ((1 << kSplitShift) - 1);
+                int32_t *var = reinterpret_cast<int32_t *>(img + I->off_chunk_var) + i * kChunk;
+                uint64_t *rec = reinterpret_cast<uint64_t *>(img + I->off_rec) + (size_t)chunk_info[i].x * kChunk;
+                std::fill_n(var, kChunk, -1);
+                for (int32_t x = w.b; x < w.e; ++x) {
+                    const int32_t lane0 = (x - w.b) * L, v = vs[x];
+                    std::fill_n(var + lane0, L, v);
+                    for (int32_t k = 0; k < deg(v); ++k) {
+                        const ChunkRec &r = recs[vptr[v] + k];
+                        P.push(lane0 + k % L, r);
+                        var[lane0 + k % L] += (int32_t)r.neg << 20;
+                    }
+                }
+                P.place(0, nslot, false);
+                for (int32_t sl = 0; sl < nslot; ++sl)
+                    for (int l = 0; l < kChunk; ++l)
+                        rec[(size_t)(sl / 2) * 2 * kChunk + (size_t)l * 2 + (sl & 1)] =
+                            pack_rec(P.out[(size_t)sl * kChunk + l]);
+                if (debug_banks) {
+                    model_cycles += chunk_gather_cycles(P.out, nslot);
+                    model_gathers += 3 * (int64_t)nslot;
+                }
+            };
+            auto split_chunk = [&](size_t i, ChunkPlacer &P) {
+                const Chunk &w = sp[i];
+                const int32_t L = 1 << w.lg, pairs = sp_info[i].y;
+                int2 *var = reinterpret_cast<int2 *>(img + I->off_sp_var) + i * kChunk;
+                uint64_t *rec = reinterpret_cast<uint64_t *>(img + I->off_sp_rec) + (size_t)sp_info[i].x * 2 * kChunk;
+                int32_t n1[kChunk] = {};
+                for (int32_t x = w.b; x < w.e; ++x)
+                    for (int32_t k = 0; k < deg(vs[x]); ++k) {
+                        const ChunkRec &r = recs[vptr[vs[x]] + k];
+                        const int32_t lane = (x - w.b) * L + k % L;
+                        n1[lane] += (int32_t)r.neg;
+                        P.push(lane, r);
+                    }
+                for (int l = 0; l < kChunk; ++l) {
+                    const int32_t x = w.b + (l >> w.lg);
+                    const uint32_t kk = (uint32_t)(2 * pairs - 2 * n1[l]) * 0x01010101u - (uint32_t)n1[l] +
+                                        (l % L ? 0u : 0x80808080u);
+                    var[l] = make_int2(x < w.e ? vs[x] : -1, (int32_t)kk);
+                }
+                P.place(0, 2 * pairs, false);
+                for (int32_t sl = 0; sl < 2 * pairs; ++sl)
+                    for (int l = 0; l < kChunk; ++l)
+                        rec[(size_t)(sl / 2) * 2 * kChunk + (size_t)l * 2 + (sl & 1)] =
+                            pack_rec(P.out[(size_t)sl * kChunk + l]);
+            };
+            // a chunk is placed in two parts: slots below ws, slots from ws on
+            auto sweep_chunk = [&](size_t i, ChunkPlacer &P) {
+                const SweepChunk &w = bl[i];
+                const int32_t nslot = bl_info[i].y, lg = bl_info[i].z, ws = bl_info[i].w, L = 1 << lg;
+                int32_t *var = reinterpret_cast<int32_t *>(img + I->off_bl_var) + i * kChunk;
+                std::fill_n(var, kChunk, -1);
+                // clauses [from, to) of v in one lane; its lane word for `slots`
+                // slots (padding among them)
+                auto push = [&](int lane, int32_t v, int32_t from, int32_t to) {
+                    for (int32_t k = from; k < to; ++k)
+                        P.push(lane, recs[vptr[v] + k]);
+                };
+                auto lane_word = [&](int32_t v, int32_t slots) {
+                    for (int32_t q = vptr[v]; q < vptr[v + 1]; ++q)
+                        slots -= (int32_t)recs[q].neg;
+                    return v | (int32_t)((uint32_t)slots << 20);
+                };
+                if (lg) {
+                    for (int32_t x = w.b; x < w.e; ++x) {
+                        const int32_t v = vs[w.c0 + x], l = (x - w.b) * L;
+                        for (int32_t k = 0; k < deg(v); ++k)
+                            push(l + k % L, v, k, k + 1);
+                        var[l] = lane_word(v, L * nslot);
+                    }
+                    P.place(0, nslot, true);
+                } else {
+                    for (int32_t x = w.b; x < w.e; ++x) {
+                        const int32_t hv = paired(w, x), l = 2 * (x - w.b);
+                        push(l, hv, 0, std::min(ws, deg(hv)));
+                        var[l] = lane_word(hv, 2 * nslot - ws);
+                        if (w.P - 1 - x > x) {
+                            const int32_t v = paired(w, w.P - 1 - x);
+                            push(l + 1, v, 0, deg(v));
+                            var[l + 1] = lane_word(v, ws);
+                        }
+                    }
+                    P.place(0, ws, true);
+                    for (int32_t x = w.b; x < w.e; ++x) {
+                        const int32_t hv = paired(w, x), l = 2 * (x - w.b);
+                        push(l, hv, ws, std::min(nslot, deg(hv)));
+                        push(l + 1, hv, nslot, deg(hv));
+                    }
+                    P.place(ws, nslot - ws, true);
+                }
+                for (int32_t sl = 0; sl < nslot; ++sl) {
+                    uint32_t *block = reinterpret_cast<uint32_t *>(img + I->off_bl_rec) +
+                                      ((uint32_t)bl_info[i].x + (uint32_t)(sl / 8 * kBlockBytes)) / 4;
+                    const int last = std::min(nslot, (sl / 8 + 1) * 8) - 1;
+                    for (int l = 0; l < kChunk; ++l) {
+                        const ChunkRec &r = P.out[(size_t)sl * kChunk + l];
+                        if (r.neg)
+                            block[l] |= 0xFu << (4 * (last - sl));
+                        const uint64_t x = pack_rec_pair(r);
+                        std::memcpy(block + (kBlockSign + sl % 8 / 2 * kBlockRow) / 4 + l * 4 + sl % 2 * 2, &x, 8);
+                    }
+                }
+            };
+            const size_t n_wh = wh.size(), n_sp = sp.size(), total = n_wh + n_sp + bl.size();
+            std::atomic<size_t> next{0};
+            run_workers(threads, [&] {
+                ChunkPlacer P((int32_t)align_up(std::max(dmax, kSlotUnroll), kSlotUnroll), bank_schedule, dummy);
+                for (size_t i; (i = next.fetch_add(1)) < total;)
+                    if (i < n_wh)
+                        whiten_chunk(i, P);
+                    else if (i < n_wh + n_sp)
+                        split_chunk(i - n_wh, P);
+                    else
+                        sweep_chunk(i - n_wh - n_sp, P);
+            });
+            if (debug_banks && model_gathers)
+                std::fprintf(stderr, "nmc: %d chunks, %lld slot gathers, modeled %.3f LDS cycles per gather\n",
+                             I->n_chunks, (long long)model_gathers, (double)model_cycles / (double)model_gathers);
         }
         *out = I.release();
         return ok();

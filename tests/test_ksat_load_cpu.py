@@ -1,6 +1,7 @@
 """Loading k-SAT instances on the host: layouts, threads, limits."""
 import subprocess
 import sys
+import time
 
 import numpy as np
 import pytest
@@ -59,3 +60,24 @@ def test_split_layout_only_where_it_fits():
     large = per_variable(13000)
     assert per_variable(9500) > 1.2 * large
     assert per_variable(10000) < 1.05 * large
+
+
+def test_load_cost(monkeypatch):
+    """What placing the records by LDS bank adds to a load, in CPU time of all
+    threads: four times a load without placement is the limit (measured: 2.2
+    times; placing one address order at a time 6.2 times for two layouts, 4.5
+    times for one)."""
+    cp, lits = instances.gen_ksat(20000, "9.8", 4, 5)
+
+    def cpu_s():
+        best = np.inf
+        for _ in range(4):
+            t = time.process_time()
+            nmc.Instance.ksat(20000, cp, lits)
+            best = min(best, time.process_time() - t)
+        return best
+
+    placed = cpu_s()
+    monkeypatch.setenv("NMC_KSAT_BANK_SCHEDULE", "0")
+    unplaced = cpu_s()
+    assert placed < 4 * unplaced, (placed, unplaced)
