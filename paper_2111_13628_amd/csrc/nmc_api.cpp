@@ -696,8 +696,10 @@ int nmc_ksat_load(int32_t n_vars, int32_t n_clauses, const int32_t *clause_ptr, 
         // The layouts are planned first (their chunks, variables by degree inside
         // a class, and sizes), then the records of all chunks are gathered,
         // placed and written to the image by several threads.
-        std::vector<int32_t> vs = I->order;
-        for (int32_t c = 0; c < ncol; ++c)
+        std::vector<int32_t> vs;
+        if (!I->wide)
+            vs = I->order;
+        for (int32_t c = 0; c < ncol && !I->wide; ++c)
             std::stable_sort(vs.begin() + I->color_ptr[c], vs.begin() + I->color_ptr[c + 1],
                              [&](int32_t x, int32_t y) { return deg(x) > deg(y); });
         // whitening: a class's variables in groups of 64.  A chunk of few

@@ -48,10 +48,10 @@ constexpr int kRepPerBlock = kQapRepPerBlock;  // one replica per wave
 constexpr int kBlockThreads = 64 * kRepPerBlock;
 // A wave takes one proposal per step after a sweep that accepted more than
 // this many sixteenths of its proposals, else whole rows: the two break even
-// near 0.4 accepted with 4 waves per SIMD (n = 100, 4096 replicas: 16.1 and
-// 17.2 G proposals/s at 0.42, 15.6 and 11.4 at 0.69; in a batched launch 15.5
-// and 14.4 at 0.42) and near 0.65 with one (n = 150, 256 replicas: 1.20 and
-// 1.16 at 0.68, 1.21 and 1.76 at 0.40).
+// near 0.42 accepted with 4 waves per SIMD (n = 100, 4096 replicas: 16.8 and
+// 17.1 G proposals/s at 0.42, 16.5 and 12.4 at 0.63; in a batched launch 16.6
+// and 16.3, 16.1 and 11.8) and near 0.63 with one (n = 150, 256 replicas: 1.29
+// and 1.25 at 0.62, 1.32 and 1.75 at 0.40).
 constexpr int kRowAccMany = 6, kRowAccFew = 10;
 constexpr int kQapCus = 256;
 
@@ -880,7 +880,11 @@ __device__ __forceinline__ int qap_wave_sweep_rows(const QapDev &I, const QapCal
 
 // One sweep, one proposal at a time on all 64 lanes (the algorithm of
 // qap_wave_sweep1 on the shifted matrices, the permutation staying in the
-// lanes): for sweeps where most proposals are accepted.
+// lanes): for sweeps where most proposals are accepted.  Bound by the scalar
+// and vector instructions of a proposal in turn (27 and 23 at n = 65 to 128):
+// taking the shifts and the row address out of the loop gave 3 to 4 % (batched,
+// acceptance 0.93, n = 100, 4096 replicas, 6 sweeps: 8.26 -> 7.97 ms; 7.96 by
+// qap_wave_sweep1).
 template <int KPL>
 __device__ __forceinline__ int qap_wave_sweep_pairs(const QapDev &I, const QapCall &C, const int8_t *F,
                                                     const int8_t *D, const int S, const uint8_t *cls,
@@ -899,31 +903,34 @@ __device__ __forceinline__ int qap_wave_sweep_pairs(const QapDev &I, const QapCa
         for (int a = 64 * SA; a < a_end; ++a) {
             const int la = a - 64 * SA;
             int pa = __builtin_amdgcn_readlane(pk[SA], la);
-            int fa[KPL], da[KPL];
+            int fa[KPL], fu[KPL], da[KPL];
 #pragma unroll
             for (int i = 0; i < KPL; ++i) {
                 fa[i] = F[a * S + lane + 64 * i];
+                fu[i] = fa[i] + 128;
                 da[i] = D[pa * S + pk[i]];
             }
-            // the cached row's distance at k = a: 0 when gathered, the
-            // accepted swap's D_{p_a p_b} after an accept
-            int g = 0;
+            // the cached row's distance at k = a, less 256: that of 0 when
+            // gathered, the accepted swap's D_{p_a p_b} after an accept (with
+            // it and fu the shifts by 128 cost nothing per proposal)
+            int g = -256;
 #pragma unroll
             for (int SB = SA; SB < KPL; ++SB) {
-                const int b_end = min(n, 64 * SB + 64);
-                for (int b = max(a + 1, 64 * SB); b < b_end; ++b) {
+                const int b0 = max(a + 1, 64 * SB), b_end = min(n, 64 * SB + 64);
+                const int8_t *frow = F + b0 * S + lane;
+                for (int b = b0; b < b_end; ++b, frow += S) {
                     const int lb = b - 64 * SB;
                     const int pb = __builtin_amdgcn_readlane(pk[SB], lb);
                     int db[KPL];
                     int part = 0;
 #pragma unroll
                     for (int i = 0; i < KPL; ++i) {
-                        const int fb = F[b * S + lane + 64 * i];
+                        const int fb = frow[64 * i];
                         db[i] = D[pb * S + pk[i]];
                         part += nmc_amdgcn_mul_i24(fa[i] - fb, db[i] - da[i]);
                     }
-                    const int fab = __builtin_amdgcn_readlane(fa[SB], lb) + 128;
-                    const int dab = __builtin_amdgcn_readlane(da[SB], lb) + 128;
+                    const int fab = __builtin_amdgcn_readlane(fu[SB], lb);
+                    const int dab = __builtin_amdgcn_readlane(da[SB], lb);
                     const int dc = 2 * (wave_sum(part) + fab * (2 * dab - g));
                     const int ds = __builtin_amdgcn_readlane((int)dsv, widx);
                     if (dc < ds) {
@@ -934,8 +941,8 @@ __device__ __forceinline__ int qap_wave_sweep_pairs(const QapDev &I, const QapCa
 #pragma unroll
                         for (int i = 0; i < KPL; ++i)
                             da[i] = db[i];
-                        da[SB] = lane_write(da[SB], lb, dab - 128);
-                        g = dab;
+                        da[SB] = lane_write(da[SB], lb, dab);
+                        g = dab - 128;
                         pa = pb;
                     }
                     if (++widx == 64) {
