@@ -3302,7 +3302,7 @@ int build_plans(nmc_batch *B, const std::vector<std::vector<SetPhase>> &ph, cons
         std::vector<QapJob> qj;
         std::vector<std::pair<double, int2>> kit, qit;
         size_t lds_k = 0, lds_q = 0;
-    QapBatchPlan plan_q;
+        QapBatchPlan plan_q;
         double att_k = 0, att_q = 0;
         for (size_t i = 0; i < ns; ++i) {
             const SetPhase *cur = nullptr;
@@ -4178,7 +4178,7 @@ extern "C" int nmc_batch_step(nmc_batch *B, const nmc_segment *segs, int32_t n_s
                off_bbqi = 0, off_src = 0, off_out = 0;
         int nk = 0, nq = 0, nbk = 0, nbq = 0;
         size_t lds_k = 0, lds_q = 0;
-    QapBatchPlan plan_q;
+        QapBatchPlan plan_q;
         for (int pass = 0; pass < 2; ++pass) {
             uint8_t *base = pass ? B->dev : nullptr;
             blob.host.clear();

@@ -623,8 +623,9 @@ __device__ __forceinline__ void sweep_group(const KsatDev &I, const KsatRepDev &
 // replica each, the records of a wave's next chunk are loaded while this
 // one is decided, the random words are drawn by whole waves (one generator
 // call per lane serves the wave's next 2^LG chunks), and thresholds, best
-// states and classes stay in LDS: a sweep ends with one barrier and no
-// access to device memory.
+// states and classes stay in LDS: a sweep ends with one barrier, a second one
+// if a best state was copied, and reads device memory only for threshold rows
+// of more than two words per thread.
 //
 // Measured (us per sweep at 64 to 1024 replicas, default tuning, against one
 // lane per variable with the words drawn per class, records staged in LDS at n
@@ -660,7 +661,8 @@ template <int LG>
 __global__ void __launch_bounds__(1024) ksat_split_kernel(KsatDev I, KsatRepDev R, SweepCall C) {
     extern __shared__ __align__(16) uint8_t smem[];
     constexpr int PER = kChunk >> LG;  // variables of a chunk
-    // record pairs of the next chunk loaded ahead: 48 clauses per variable
+    // record pairs of the next chunk loaded ahead: 48, 64 and 96 clauses per
+    // variable on 4, 8 and 16 lanes
     constexpr int PRE = LG == 2 ? kSplitAhead : LG == 3 ? 4 : 3;
     const int n = I.n, g = blockIdx.x;
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, nwaves = nthr >> 6;
