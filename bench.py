@@ -40,7 +40,7 @@ RPW = 0  # k-SAT replicas per sweep workgroup (0: the library's default, 4)
 # VALU lane-operations the sweep kernel issues per (variable, clause slot) for
 # its 4 replicas, and per variable for the acceptance step, counted in the
 # kernel's instruction stream.
-OPS_PER_SLOT = 9.0
+OPS_PER_SLOT = 6.0
 OPS_PER_VAR = 62.0
 # VALU lane rate behind the published 157.3 TFLOP/s fp32 vector figure (two
 # flops per fused multiply-add): 256 CUs x 128 lane-operations x 2.4 GHz
