@@ -296,7 +296,7 @@ def bench_qap(nmc, torch, seed, sweeps_only=0, sweeps_offset=0, curve=0):
     achieved = kps * reads
     roofline = {"bound": "lds", "achieved": achieved / 1e12, "peak": LDS_LANE_READS / 1e12,
                 "unit": "T lane-reads/s", "frac": achieved / LDS_LANE_READS, "traffic": None,
-                "kernel": "qap_sweep_kernel", "kernel_ms_per_launch": kt["ms"] / max(1, kt["launches"]),
+                "kernel": "qap_rows_kernel", "kernel_ms_per_launch": kt["ms"] / max(1, kt["launches"]),
                 "launches": kt["launches"],
                 # the scope table's model: ~3(n - 2) LDS lane-accesses per proposal
                 # (98 permutation bytes + 196 distance gathers at n = 100) against
