@@ -456,8 +456,11 @@ int nmc_replicas_info(const nmc_replicas *rep, int32_t *n_replicas, uint64_t *se
  * ------------------------------------------------------------------------- */
 
 /* block_threads: threads per workgroup of the k-SAT sweep kernel (64..1024,
- * multiple of 64; 0 = default 1024).  QAP sweeps always run one replica per
- * wave, 16 per 1024-thread workgroup, and ignore it. */
+ * multiple of 64; 0 = default 1024).  Instances of small colour classes run
+ * several lanes per variable at the default size, in workgroups of their own
+ * size, and with 2048 clauses or fewer (up to 4096 replicas) at every size.
+ * QAP sweeps run one replica per wave, 4, 8 or 16 per workgroup by the number
+ * of replicas, and ignore it. */
 int nmc_set_tuning(nmc_replicas *rep, int32_t block_threads);
 
 /* k-SAT replicas per sweep workgroup: 4 (0 = default; one group, bits 0..3
